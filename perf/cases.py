@@ -313,6 +313,52 @@ def run(s):
     return {"out": s.out, "perm": s.perm}
 
 
+# ---- the same step in 64 bits ----
+_EXACT_FLOPS = 1e14                                   # above: too long in 64 bits
+
+
+def exact(case, seed):
+    """The outputs of `run` in plain 64-bit torch; the values are drawn again in the order in which `prepare` draws them."""
+    if work(case)["flops"] > _EXACT_FLOPS:
+        return None
+    proj, _ = _projections(case)
+    layers, T, n, swap = case["layers"], case["tokens"], case["adapters"], case["swap"]
+    rank_of, steps = _batch(case, seed)
+    gen = torch.Generator(device="cuda").manual_seed(1000003 * (seed % 1000003) + 7)
+    adapters = [_adapter_values(gen, rank_of[a], proj, layers) for a in range(n + 2 * swap)]
+    W = [[_normal(gen, (d_out, d_in), 0.02) for d_in, d_out in proj] for _ in range(layers)]
+    groups = [[0]] if len(proj) == 1 else [[0, 1, 2], [3], [4, 5], [6]]
+    x = [{g[0]: _normal(gen, (T, proj[g[0]][0]), 1.0) for g in groups} for _ in range(layers)]
+    bias = {}
+    if case["shape"] == "qwen7b":
+        bias = {(l, p): _normal(gen, (proj[p][1],), 1.0) for l in range(layers) for p in (0, 1, 2)}
+    unit = sum(a + b for a, b in proj)
+    out = []
+    for ids in steps:
+        rows = {int(a): torch.from_numpy(np.flatnonzero(ids == a)).cuda() for a in np.unique(ids) if a >= 0}
+        outs = []
+        for l in range(layers):
+            for g in groups:
+                x64, ys = x[l][g[0]].double(), []
+                for p in g:
+                    d_in, d_out = proj[p]
+                    y = x64 @ W[l][p].double().t()
+                    if (l, p) in bias:
+                        y += bias[l, p].double()
+                    before = l * unit + sum(a + b for a, b in proj[:p])
+                    for a, at in rows.items():
+                        r = rank_of[a]
+                        mats = adapters[a][r * before:r * (before + d_in + d_out)].double()
+                        v = x64[at] @ mats[:r * d_in].view(r, d_in).t()
+                        y[at] += float(np.float32(wl.ALPHA / r)) * (v @ mats[r * d_in:].view(d_out, r).t())
+                    ys.append(y)
+                if case["gated"] and len(g) == 2:
+                    ys = [torch.nn.functional.silu(ys[0]) * ys[1]]
+                outs += ys
+        out.append(outs)
+    return {"out": out, "perm": None}
+
+
 def work(case):
     proj, _ = _projections(case)
     rank_of, steps = _batch(case, 0)
