@@ -67,7 +67,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     constexpr int QPT = XQ + WQ;
     static_assert(BM % (8 * NWV) == 0 && BN % (8 * NWV) == 0, "tile/waves");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
-    static_assert(NS >= 2 && NS <= 5 && (NS - 1) * QPT <= 63, "stages / vmcnt range");
+    static_assert(NS >= 2 && NS <= 7 && (NS - 1) * QPT <= 63, "stages / vmcnt range");
     static_assert(NS * STAGE_B <= 160 * 1024, "LDS");
 
     __shared__ __attribute__((aligned(1024))) uint8_t ring[NS * STAGE_B];
@@ -172,11 +172,23 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
         woff[q] = (uint32_t)n * (uint32_t)K + (uint32_t)(c * 8 + kt_begin * kTK64);
         w_up[q] = GLU && ((((wave * WQ + q) * 8) >> 5) & 1);
     }
+    // k_rot (fused path up to 128 tokens, K a multiple of 2048): column tile n starts its walk over K at K tile n and
+    // wraps around.  With all workgroups at the same K offset and rows a multiple of 4 KB apart, the weight stream asks few
+    // memory channels at a time: gate|up of Llama-8B (235 MB of W) at one token 66 -> 52 us, at 32 tokens 75 -> 61 (128-row
+    // tiles).  Rows of 7 KB (K = 3584) do not need it (75 and 76 us), a 256-row tile gains nothing (step of 256 tokens
+    // 231 us either way), and several row tiles lose by spreading over x (640 tokens, q|k|v: 60 -> 83 us).
+    constexpr bool ROT = FUSED && BM <= 128;
+    const int rot = ROT && a.k_rot ? tile_n % nk : 0;
     const uint32_t cp_x = ring_addr + wave * XQ * 1024;
     const uint32_t cp_w = ring_addr + BM * kRowB + wave * WQ * 1024;
     // copy instructions [q_begin, q_end) of tile t of this workgroup's K range; the W rows (from HBM) go first
     auto copy_part = [&](int t, int stage, int q_begin, int q_end) {
-        const uint32_t k0 = (uint32_t)t * kTK64, so = (uint32_t)stage * STAGE_B;
+        int tk = t;
+        if (ROT) {                                           // see above: where this workgroup's walk over K starts
+            tk += rot;
+            if (tk >= nk) tk -= nk;
+        }
+        const uint32_t k0 = (uint32_t)tk * kTK64, so = (uint32_t)stage * STAGE_B;
 #pragma unroll
         for (int q = 0; q < QPT; ++q) {
             if (q < q_begin || q >= q_end) continue;
@@ -243,7 +255,9 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     auto wait_for_tile = [&](int t) {
         int young = nk - 1 - t;
         if (young > NS - 2) young = NS - 2;
-        if (young >= 3) wait_copies_then_barrier<(NS >= 5 ? 3 : 0) * QPT>();
+        if (young >= 5) wait_copies_then_barrier<(NS >= 7 ? 5 : 0) * QPT>();
+        else if (young == 4) wait_copies_then_barrier<(NS >= 6 ? 4 : 0) * QPT>();
+        else if (young == 3) wait_copies_then_barrier<(NS >= 5 ? 3 : 0) * QPT>();
         else if (young == 2) wait_copies_then_barrier<(NS >= 4 ? 2 : 0) * QPT>();
         else if (young == 1) wait_copies_then_barrier<QPT>();
         else wait_copies_then_barrier<0>();
@@ -389,6 +403,22 @@ hipError_t launch_gemm_rows128_fused(const GemmArgs& a, const ShrinkArgs& none, 
         case 4:
             *name = "gemm_fused_256x128x64_w4";
             return launch_rows128<256, 128, 2, 2, true, 3>(a, none, stream);
+        // Up to 32 / 64 tokens: no copies for rows that do not exist, which leaves the copies and the LDS to W.  Llama-8B
+        // gate|up, 128-row tile -> these: 32 tokens 61 -> 56 us, 64 tokens 67 -> 61 us.
+        case 6:
+            *name = "gemm_fused_32x128x64_w4";
+            return launch_rows128<32, 128, 1, 4, true, 7>(a, none, stream);
+        case 7:
+            *name = "gemm_fused_64x128x64_w4";
+            return launch_rows128<64, 128, 2, 2, true, 6>(a, none, stream);
+        // The same with three stages, so that two workgroups fit a CU: for launches of more tiles than CUs (Qwen2.5-7B
+        // gate|up, 296 tiles, 32 tokens: shrink launch + 75 us -> 73 us with the shrink inside).
+        case 8:
+            *name = "gemm_fused_32x128x64_w4_pair";
+            return launch_rows128<32, 128, 1, 4, true, 3>(a, none, stream);
+        case 9:
+            *name = "gemm_fused_64x128x64_w4_pair";
+            return launch_rows128<64, 128, 2, 2, true, 3>(a, none, stream);
         case 5:
             *name = "gemm_fused_256x256x64_w4";
             return launch_rows128<256, 256, 2, 2, true, 2>(a, none, stream);
@@ -401,9 +431,19 @@ hipError_t launch_gemm_rows128_fused(const GemmArgs& a, const ShrinkArgs& none, 
 hipError_t launch_gemm_rows128_glu(const GemmArgs& a, const ShrinkArgs& none, int variant, hipStream_t stream,
                                    const char** name)
 {
-    if (variant == 1) {
-        *name = "gemm_glu_128x128x64_w4";
-        return launch_rows128<128, 128, 2, 2, true, 4, true>(a, none, stream);
+    switch (variant) {
+        case 1:
+            *name = "gemm_glu_128x128x64_w4";
+            return launch_rows128<128, 128, 2, 2, true, 4, true>(a, none, stream);
+        case 10:
+            *name = "gemm_glu_128x128x64_w8";
+            return launch_rows128<128, 128, 4, 2, true, 4, true>(a, none, stream);
+        case 7:
+            *name = "gemm_glu_64x128x64_w4";
+            return launch_rows128<64, 128, 2, 2, true, 6, true>(a, none, stream);
+        case 9:
+            *name = "gemm_glu_64x128x64_w4_pair";
+            return launch_rows128<64, 128, 2, 2, true, 3, true>(a, none, stream);
     }
     *name = "gemm_glu_256x128x64_w8";
     return launch_rows128<256, 128, 4, 2, true, 3, true>(a, none, stream);
@@ -416,6 +456,14 @@ hipError_t launch_gemm_rows128_splitk(const GemmArgs& a, const ShrinkArgs& sa, i
         case 1:
             *name = "gemm_splitk_shrink_128x128x64_w4";
             return launch_rows128<128, 128, 2, 2, false, 4>(a, sa, stream);
+        // up to 32 / 64 tokens (see the fused variants).  Llama-8B q|k|v, o, down at 32 tokens: 16.5, 13.1, 29.8 -> 15.0,
+        // 13.5, 25.5 us; at 64 tokens 19.4, 14.0, 30.7 -> 17.0, 13.1, 28.6 us
+        case 4:
+            *name = "gemm_splitk_shrink_32x128x64_w4";
+            return launch_rows128<32, 128, 1, 4, false, 7>(a, sa, stream);
+        case 5:
+            *name = "gemm_splitk_shrink_64x128x64_w4";
+            return launch_rows128<64, 128, 1, 4, false, 6>(a, sa, stream);
         case 2:
             *name = "gemm_splitk_shrink_256x128x64_w4";
             return launch_rows128<256, 128, 2, 2, false, 3>(a, sa, stream);

@@ -74,8 +74,28 @@ struct Layout {
     size_t total = 0;
 };
 
-// split-K GEMM variants 3, 4 and 7 use 128-row tiles, the others 256-row tiles; 6 and 7 walk K in 64-wide tiles
-int split_bm(int variant) { return (variant == 3 || variant == 4 || variant == 7) ? 128 : 256; }
+// Rows of the split-K GEMM variants' tiles.  6, 7, 9 and the small-batch variants 10 and 11 walk K in 64-wide tiles.
+constexpr int kSplit32 = 10, kSplit64 = 11;
+int split_bm(int variant)
+{
+    if (variant == kSplit32) return 32;
+    if (variant == kSplit64) return 64;
+    return (variant == 3 || variant == 4 || variant == 7) ? 128 : 256;
+}
+bool split_wide_k(int variant) { return variant == 6 || variant == 7 || variant >= 9; }
+
+// Variants of the 64-wide-K fused GEMM that only the automatic choice takes: 32- and 64-row tiles, one workgroup per
+// CU or (kFusedPair*) two.
+constexpr int kFused32 = 20, kFused64 = 21, kFusedPair32 = 22, kFusedPair64 = 23;
+constexpr int kGlu128W8 = 24;                // gate and up, 128 x 128 with eight waves
+bool fused_small(int fv) { return fv >= kFused32 && fv <= kGlu128W8; }
+bool fused_pair(int fv) { return fv == kFusedPair32 || fv == kFusedPair64; }
+// tile of the 64-wide-K fused variants that can shrink inside the launch
+void fused_tile(int fv, int& bm, int& bn)
+{
+    bm = (fv == kFused32 || fv == kFusedPair32) ? 32 : (fv == kFused64 || fv == kFusedPair64) ? 64 : ((fv == 9 || fv == kGlu128W8) ? 128 : 256);
+    bn = fv == 10 ? 256 : (fv == 11 ? 192 : 128);
+}
 
 // Device-visible address of a pointer into pinned (page-locked, mapped) host memory, or NULL when the pointer
 // is anything else (pageable host memory must never reach a kernel).
@@ -393,7 +413,7 @@ lora_status plan_forward(const lora_ctx* c, int32_t T, int32_t n, const int32_t*
         // short K at up to 256 tokens (half the K splits, half the partial tiles)
         // and up to 128 tokens a 256-row tile would copy and multiply rows that do not exist
         if (split_variant == 0)
-            split_variant = (T <= 128 || n_pad_total <= 2048 || (n_pad_total <= 4096 && K <= 8192 && T <= 256)) ? 7 : 6;
+            split_variant = T <= 32 ? kSplit32 : T <= 64 ? kSplit64 : (T <= 128 || n_pad_total <= 2048 || (n_pad_total <= 4096 && K <= 8192 && T <= 256)) ? 7 : 6;
         const int bm = split_bm(split_variant), bn = split_variant == 2 ? 64 : 128;
         const long tiles = tiles_of(bm, bn);
         // The 64-wide-K kernels give a quarter of the CUs workgroups that only shrink, from the start (a shrink
@@ -401,7 +421,7 @@ lora_status plan_forward(const lora_ctx* c, int32_t T, int32_t n, const int32_t*
         // Only while those workgroups can finish the items meanwhile: a batch spread over hundreds of adapters
         // has more shrink work than tile work, and every workgroup takes its share after its tile instead.
         const long pieces_bound = (long)n * std::min<long>(T, (long)c->n_resident + (T + kPieceRows - 1) / kPieceRows);
-        dyn_shrink = c->n_resident > 0 && (split_variant == 6 || split_variant == 7 || split_variant == 9) &&
+        dyn_shrink = c->n_resident > 0 && split_wide_k(split_variant) &&
                      pieces_bound * std::max(1, K / 2048) <= 512;
         const long target = dyn_shrink ? c->n_cus * 3 / 4 : c->n_cus;
         // K splits, at most 8, by a cost model in microseconds: a workgroup walking all of K moves (bm + bn) K
@@ -412,7 +432,7 @@ lora_status plan_forward(const lora_ctx* c, int32_t T, int32_t n, const int32_t*
             S = c->cfg.split_k;
         } else {
             const double t_full = (double)(bm + bn) * K * 2.0 / 48e3;
-            const double t_part = (double)Mpad * (double)n_pad_total * 8.0 / 5e6;
+            const double t_part = (double)((T + bm - 1) / bm * bm) * (double)n_pad_total * 8.0 / 5e6;
             double best = 0.0;
             for (int cand = 1; cand <= 8; ++cand) {
                 // a single K range takes the fused path instead (below): every CU can hold a tile and there are
@@ -1079,8 +1099,8 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         {
             LaunchScope ls(c, s, "gemm_splitk");
             const char* name = nullptr;
-            // 6, 7: 64-wide K tiles; 8: the 32-wide 256 x 128 kernel (its own variant 0); 1 .. 5: 32-wide variants
-            const hipError_t le = (variant == 6 || variant == 7 || variant == 9)
+            // 6, 7, 9 ..: 64-wide K tiles; 8: the 32-wide 256 x 128 kernel (its own variant 0); 1 .. 5: 32-wide variants
+            const hipError_t le = split_wide_k(variant)
                                       ? launch_gemm_rows128_splitk(a, shrink, variant == 9 ? 2 : variant - 6, s, &name)
                                       : launch_gemm_splitk(a, shrink, variant == 8 ? 0 : variant, s, &name);
             if (HIP_FAIL(le)) return LORA_ERR_HIP;
@@ -1107,14 +1127,23 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         // ---- shrink, then base GEMM with the expand in its epilogue ----
         int fv = c->tune[LORA_TUNE_FUSED_VARIANT];
         const bool auto_variant = fv == 0 && !glu;
-        // gate and up with their product: the 64-wide-K kernel up to 1024 tokens (128-row tiles up to 128), the
-        // register-staged 256 x 256 tile above
-        if (glu) fv = T <= 128 ? 9 : (T <= kSplitMaxTokens ? 8 : 0);
+        // Up to 64 tokens the tile has 32 or 64 rows; with more such tiles than CUs, the variant of which two workgroups
+        // share a CU.
+        auto small_variant = [&](int one, int pair, long tiles) { return tiles <= c->n_cus ? one : pair; };
+        // gate and up with their product: the 64-wide-K kernel up to 1024 tokens (64-row tiles up to 64, 128-row tiles up
+        // to 128, with eight waves where the tiles fill at least half the chip: Llama-8B, 99 tokens, 69 us with four, 66 with
+        // eight), the register-staged 256 x 256 tile above
+        if (glu)
+            fv = T <= 64    ? small_variant(kFused64, kFusedPair64, tiles_of(64, 128))
+                 : T <= 128 ? (tiles_of(128, 128) >= c->n_cus / 2 ? kGlu128W8 : 9)
+                            : (T <= kSplitMaxTokens ? 8 : 0);
         if (auto_variant) {
             fv = pick_fused_variant(c->n_cus, tiles_of);
             // small batch: bound by the copies, not by the MFMA issue: whole-line tiles, every wave copies
             // (128-row tiles up to 128 tokens)
-            if (T <= kSplitMaxTokens) fv = T <= 128 ? 9 : (fv == 4 ? 8 : (fv == 3 ? 9 : 10));
+            if (T <= 64)
+                fv = T <= 32 ? small_variant(kFused32, kFusedPair32, tiles_of(32, 128)) : small_variant(kFused64, kFusedPair64, tiles_of(64, 128));
+            else if (T <= kSplitMaxTokens) fv = T <= 128 ? 9 : (fv == 4 ? 8 : (fv == 3 ? 9 : 10));
             // between 129 and 1024 tokens the launch is bound by what a workgroup moves through its CU: rounds
             // of workgroups over the CUs times the rows (x and W) of a tile; near ties go to the larger tile
             if (T > 128 && T <= kSplitMaxTokens) {
@@ -1160,10 +1189,11 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         // for Qwen2.5-7B).  When those CUs can finish the shrink well inside the time the tiles stream, they do
         // it as the first workgroups of the GEMM launch and the separate shrink launch goes.
         int front = 0;
-        if (sa.on && fv >= 8 && fv <= 11 && T <= kSplitMaxTokens && m_split == T && !c->inline_shrink_off &&
+        if (sa.on && ((fv >= 8 && fv <= 11) || fused_small(fv)) && T <= kSplitMaxTokens && m_split == T && !c->inline_shrink_off &&
             c->tune[LORA_TUNE_INLINE_SHRINK] != LORA_INLINE_SHRINK_OFF) {
-            const int bm = fv == 9 ? 128 : 256, bn = fv == 10 ? 256 : (fv == 11 ? 192 : 128);
-            const long idle = c->n_cus - tiles_of(bm, bn);
+            int bm, bn;
+            fused_tile(fv, bm, bn);
+            const long idle = (fused_pair(fv) ? 2 * c->n_cus : c->n_cus) - tiles_of(bm, bn);
             // unsplit up to K = 4096 (two rounds of loads per item): the tile workgroups then fetch one partial
             // result per row instead of two, behind their last K tile
             const int chunks = std::max(1, std::min<int>(kMaxShrinkChunks, K / 4096));
@@ -1199,10 +1229,13 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             a.wait_spins = wait_test > 0 ? wait_test : kShrinkWaitSpins;
             a.sync = c->dev<uint32_t>(c->L.off_header) + 8;
             a.flags = c->d_flags();
-            // 8 .. 11, 13, 14: 64-wide K tiles through the copy instruction; 12: the 32-wide 256 x 256 eight-wave kernel
-            const hipError_t le = glu ? (fv == 0 ? launch_gemm_staged_glu(a, s, &name) : launch_gemm_rows128_glu(a, sa, fv - 8, s, &name))
-                                  : ((fv >= 8 && fv <= 11) || fv == 13 || fv == 14)
-                                      ? launch_gemm_rows128_fused(a, sa, fv >= 13 ? fv - 9 : fv - 8, s, &name)
+            // rows of W a multiple of 4 KB apart, one row tile
+            a.k_rot = T <= 128 && K % 2048 == 0 ? 1 : 0;
+            // 8 .. 11, 13, 14, 20 .. 23: 64-wide K tiles through the copy instruction; 12: the 32-wide 256 x 256 eight-wave kernel
+            const int wide = fused_small(fv) ? fv - kFused32 + 6 : fv >= 13 ? fv - 9 : fv - 8;
+            const hipError_t le = glu ? (fv == 0 ? launch_gemm_staged_glu(a, s, &name) : launch_gemm_rows128_glu(a, sa, wide, s, &name))
+                                  : ((fv >= 8 && fv <= 11) || fv == 13 || fv == 14 || fused_small(fv))
+                                      ? launch_gemm_rows128_fused(a, sa, wide, s, &name)
                                       // 0 (the big tile of the automatic choice), 15, 16: tiles staged through registers
                                       : (fv == 0 || (fv >= 15 && fv <= 18)) ? launch_gemm_staged_fused(a, fv == 0 ? 0 : fv - 15, s, &name)
                                                                           : launch_gemm_fused(a, fv == 12 ? 0 : fv, s, &name);

@@ -89,3 +89,20 @@ def test_argument_errors():
         assert e.value.status == B.LORA_ERR_INVALID_ARG
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("n_tokens,kernel", [(1, "gemm_glu_64x128x64_w4"), (64, "gemm_glu_64x128x64_w4"), (65, "gemm_glu_128x128x64_w4")])
+def test_smallest_batches(n_tokens, kernel):
+    _run(wl.config2(shrink=8, n_tokens=n_tokens), kernel)
+    _run(wl.qwen_decode(shrink=8, n_tokens=n_tokens), kernel)
+
+
+def test_gated_tile_of_eight_waves():
+    # at least half as many 128 x 128 tiles of both matrices as CUs: 2 x 8192 columns; a short K keeps the oracle quick
+    rng = np.random.default_rng(5)
+    ids = rng.integers(-1, 6, size=101).astype(np.int32)
+    w = wl.custom("glu_wide", 5, [(128, 8200), (128, 8200)], ["gate", "up"], 6, 16, wl.BUCKET_SORTED, ids, {i: 8 * (1 + i % 2) for i in range(6)})
+    _run(w, "gemm_glu_128x128x64_w8")
+    # more 64-row tiles than CUs: two workgroups on a CU
+    w = wl.custom("glu_wider", 6, [(128, 16648), (128, 16648)], ["gate", "up"], 6, 16, wl.BUCKET_SORTED, ids[:40], {i: 8 * (1 + i % 2) for i in range(6)})
+    _run(w, "gemm_glu_64x128x64_w4_pair")

@@ -43,3 +43,14 @@ def test_shrink_inside_the_fused_launch(mode, variant):
     run_and_check(wl.config2(shrink=8, n_tokens=300), path=B.LORA_PATH_FUSED, tuning=tuning, packed=True)
     run_and_check(wl.config4(shrink=8), path=B.LORA_PATH_FUSED, tuning=tuning, packed=True)
     run_and_check(wl.qwen_decode(shrink=4, n_tokens=200), path=B.LORA_PATH_FUSED, tuning=tuning)
+
+
+@pytest.mark.parametrize("path", [B.LORA_PATH_FUSED, B.LORA_PATH_SPLITK])
+@pytest.mark.parametrize("n_tokens", [1, 31, 32, 33, 63, 64, 65])
+def test_small_batch_tiles_and_their_edges(n_tokens, path):
+    # 32- and 64-row tiles and the first size behind each.  K of gate|up is 512, 448 (shrink 8) and 2048 (shrink 2, where the
+    # fused launch starts its column tiles at different places of K)
+    run_and_check(wl.config2(shrink=8, n_tokens=n_tokens), path=path, packed=True)
+    run_and_check(wl.qwen_decode(shrink=8, n_tokens=n_tokens), path=path)
+    if n_tokens in (1, 33):
+        run_and_check(wl.config2(shrink=2, n_tokens=n_tokens), path=path, packed=True)
