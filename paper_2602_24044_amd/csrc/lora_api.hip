@@ -130,17 +130,30 @@ int auto_split_cap(int N, int n_cus)
     return std::max(1, std::min(16, s));
 }
 
-// Tile shape of the fused GEMM: rounds of workgroups over the CUs times the cost of one tile, with the
-// per-flop efficiencies measured for the three shapes (256x256: 1, 256x128: 0.78, 128x128: 0.65).  Large
-// problems take the big tile; a projection with few big tiles (k/v at a few thousand tokens) fills the chip
-// better with small ones.
+// Tile shape of the register-staged fused GEMM: rounds of workgroups over the CUs times the measured time of a round
+// relative to one of 256 x 256 tiles (K = 4096: 116 us; 256 x 192: 92; 128 x 256: 73; 128 x 128, the 32-wide kernel: 45).
+// Large problems take the big tile, and so do near ties; a projection with few big tiles (o and down at a few thousand
+// tokens) fills the chip better with smaller ones.  Llama-8B, 256 x 256 tiles -> this choice: 2100 tokens o 120 -> 94 us,
+// down 351 -> 281; 1300 tokens (before: 256 x 128 tiles of the 32-wide kernel) o 80 -> 73, down 232 -> 216, q|k|v 120 -> 94.
+// tail: cost of 256 x 256 tiles when the rows behind the full rounds go to the split-K path (0: they do not).
+constexpr int kStaged192 = 30, kStaged128 = 31;
 template <typename TilesOf>
-int pick_fused_variant(int n_cus, TilesOf&& tiles_of)
+int pick_fused_variant(int n_cus, TilesOf&& tiles_of, double tail)
 {
-    auto rounds = [&](int bm, int bn) { return (double)((tiles_of(bm, bn) + n_cus - 1) / n_cus); };
-    const double big = rounds(256, 256) * 1.0, mid = rounds(256, 128) * (0.5 / 0.78), small = rounds(128, 128) * (0.25 / 0.65);
-    if (big <= mid * 1.1 && big <= small * 1.1) return 0;      // near ties go to the big tile (measured)
-    return mid <= small ? 4 : 3;
+    const struct { int v, bm, bn; double round; } cand[] = {
+        {0, 256, 256, 1.0}, {kStaged192, 256, 192, 0.78}, {kStaged128, 128, 256, 0.63}, {3, 128, 128, 0.385}};
+    int v = 0;
+    double best = 0.0;
+    for (const auto& cd : cand) {
+        const long tiles = tiles_of(cd.bm, cd.bn);
+        double cost = (double)((tiles + n_cus - 1) / n_cus) * cd.round;
+        if (cd.v == 0 && tail > 0.0) cost = std::min(cost, tail);
+        if (best == 0.0 || cost < best * 0.97) {
+            best = cost;
+            v = cd.v;
+        }
+    }
+    return v;
 }
 
 bool valid_config(const lora_config* c)
@@ -1132,39 +1145,18 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         auto small_variant = [&](int one, int pair, long tiles) { return tiles <= c->n_cus ? one : pair; };
         // gate and up with their product: the 64-wide-K kernel up to 1024 tokens (64-row tiles up to 64, 128-row tiles up
         // to 128, with eight waves where the tiles fill at least half the chip: Llama-8B, 99 tokens, 69 us with four, 66 with
-        // eight), the register-staged 256 x 256 tile above
+        // eight), the register-staged 256 x 256 tile above 1024 and, where its tiles fill three quarters of the chip, above 256
         if (glu)
             fv = T <= 64    ? small_variant(kFused64, kFusedPair64, tiles_of(64, 128))
                  : T <= 128 ? (tiles_of(128, 128) >= c->n_cus / 2 ? kGlu128W8 : 9)
-                            : (T <= kSplitMaxTokens ? 8 : 0);
-        if (auto_variant) {
-            fv = pick_fused_variant(c->n_cus, tiles_of);
-            // small batch: bound by the copies, not by the MFMA issue: whole-line tiles, every wave copies
-            // (128-row tiles up to 128 tokens)
-            if (T <= 64)
-                fv = T <= 32 ? small_variant(kFused32, kFusedPair32, tiles_of(32, 128)) : small_variant(kFused64, kFusedPair64, tiles_of(64, 128));
-            else if (T <= kSplitMaxTokens) fv = T <= 128 ? 9 : (fv == 4 ? 8 : (fv == 3 ? 9 : 10));
-            // between 129 and 1024 tokens the launch is bound by what a workgroup moves through its CU: rounds
-            // of workgroups over the CUs times the rows (x and W) of a tile; near ties go to the larger tile
-            if (T > 128 && T <= kSplitMaxTokens) {
-                const struct { int v, bm, bn; } cand[] = {{10, 256, 256}, {11, 256, 192}, {8, 256, 128}, {9, 128, 128}};
-                double best = 0.0;
-                for (const auto& cd : cand) {
-                    const double cost = (double)((tiles_of(cd.bm, cd.bn) + c->n_cus - 1) / c->n_cus) * (cd.bm + cd.bn);
-                    if (best == 0.0 || cost < best * 0.97) {
-                        best = cost;
-                        fv = cd.v;
-                    }
-                }
-            }
-        }
+                            : (T <= 256 || (T <= kSplitMaxTokens && tiles_of(256, 256) < c->n_cus * 3 / 4) ? 8 : 0);
         // A last round of 256 x 256 tiles that fills less than half the chip costs as much as a full one.  When
-        // the rows behind the full rounds are few enough for the split-K path, the fused launch stops at the
+        // the rows behind the full rounds are few enough for the split-K path, the fused launch can stop at the
         // full rounds and those rows take the split-K path (their shrink results are there already), which
         // spreads them over every CU.
-        int m_split = T;
-        int tail_S = 1;
-        if (auto_variant && fv == 0 && c->cfg.path == LORA_PATH_AUTO && T > kSplitMaxTokens) {
+        int m_full = T, tail_S = 1;
+        double tail_cost = 0.0;
+        if (auto_variant && c->cfg.path == LORA_PATH_AUTO && T > kSplitMaxTokens) {
             const long tiles_m_big = (T + 255) / 256, tiles_big = tiles_of(256, 256), tiles_n_big = tiles_big / tiles_m_big;
             const long full = tiles_big / c->n_cus, rest = tiles_big % c->n_cus;
             if (full >= 1 && rest > 0 && rest <= c->n_cus / 2) {
@@ -1179,12 +1171,44 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                     ts = std::min<long>(ts, std::max(1, (K / kBK) / 2));
                     ts = std::min<long>(ts, (long)(scr.part_elems / ((size_t)tail_pad * (size_t)n_pad_total)));
                     if (ts >= 2) {
-                        m_split = (int)(m_tiles_main * 256);
+                        m_full = (int)(m_tiles_main * 256);
                         tail_S = (int)ts;
+                        // the tail's two launches count as half a round of 256 x 256 tiles (measured: 0.54 for 340 rows of Llama-8B
+                        // q|k|v, 0.39 and 0.35 for 384 rows of Llama-70B o and down)
+                        tail_cost = (double)((m_tiles_main * tiles_n_big + c->n_cus - 1) / c->n_cus) + 0.5;
                     }
                 }
             }
         }
+        if (auto_variant) {
+            fv = pick_fused_variant(c->n_cus, tiles_of, tail_cost);
+            // small batch: bound by the copies, not by the MFMA issue: whole-line tiles, every wave copies
+            // (128-row tiles up to 128 tokens)
+            if (T <= 64)
+                fv = T <= 32 ? small_variant(kFused32, kFusedPair32, tiles_of(32, 128)) : small_variant(kFused64, kFusedPair64, tiles_of(64, 128));
+            else if (T <= 128) fv = 9;
+            // between 129 and 1024 tokens the launch is bound by what a workgroup moves through its CU: rounds
+            // of workgroups over the CUs times the rows (x and W) of a tile; near ties go to the larger tile
+            else if (T <= kSplitMaxTokens) {
+                const struct { int v, bm, bn; } cand[] = {{10, 256, 256}, {11, 256, 192}, {8, 256, 128}, {9, 128, 128}};
+                const int staged = fv;
+                double best = 0.0;
+                for (const auto& cd : cand) {
+                    const double cost = (double)((tiles_of(cd.bm, cd.bn) + c->n_cus - 1) / c->n_cus) * (cd.bm + cd.bn);
+                    if (best == 0.0 || cost < best * 0.97) {
+                        best = cost;
+                        fv = cd.v;
+                    }
+                }
+                // From 257 tokens on a launch that wants the wide tiles is bound by the matrix cores: the staged tiles,
+                // although their shrink is a launch of its own (Llama-8B gate|up: 400 tokens 158 -> 141 + 9 us, 640 tokens
+                // 245 -> 196, 777 tokens 278 -> 248, 1024 tokens 294 -> 259).  The narrower ones stay: q|k|v and o at 640 -
+                // 1024 tokens 60 and 56 us against 71 and 64.
+                if (T > 256 && (fv == 10 || fv == 11) && staged != 3) fv = staged;
+            }
+        }
+        const bool use_tail = auto_variant && fv == 0 && m_full < T;
+        const int m_split = use_tail ? m_full : T;
         // Small batches leave CUs without a tile (224 tiles of 256 x 128 for a Llama-8B gate|up, 198 of 256 x 192
         // for Qwen2.5-7B).  When those CUs can finish the shrink well inside the time the tiles stream, they do
         // it as the first workgroups of the GEMM launch and the separate shrink launch goes.
@@ -1237,7 +1261,8 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                                   : ((fv >= 8 && fv <= 11) || fv == 13 || fv == 14 || fused_small(fv))
                                       ? launch_gemm_rows128_fused(a, sa, wide, s, &name)
                                       // 0 (the big tile of the automatic choice), 15, 16: tiles staged through registers
-                                      : (fv == 0 || (fv >= 15 && fv <= 18)) ? launch_gemm_staged_fused(a, fv == 0 ? 0 : fv - 15, s, &name)
+                                      : (fv == 0 || (fv >= 15 && fv <= 18) || fv == kStaged192 || fv == kStaged128)
+                                          ? launch_gemm_staged_fused(a, fv == 0 ? 0 : fv >= kStaged192 ? fv - kStaged192 + 4 : fv - 15, s, &name)
                                                                           : launch_gemm_fused(a, fv == 12 ? 0 : fv, s, &name);
             if (HIP_FAIL(le)) return LORA_ERR_HIP;
             ls.rename(name);

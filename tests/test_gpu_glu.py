@@ -106,3 +106,10 @@ def test_gated_tile_of_eight_waves():
     # more 64-row tiles than CUs: two workgroups on a CU
     w = wl.custom("glu_wider", 6, [(128, 16648), (128, 16648)], ["gate", "up"], 6, 16, wl.BUCKET_SORTED, ids[:40], {i: 8 * (1 + i % 2) for i in range(6)})
     _run(w, "gemm_glu_64x128x64_w4_pair")
+
+
+def test_staged_gated_tile_below_1025_tokens():
+    rng = np.random.default_rng(7)
+    ids = np.repeat(rng.integers(-1, 6, size=30), 10)[:261].astype(np.int32)
+    w = wl.custom("glu_staged", 7, [(64, 14336), (64, 14336)], ["gate", "up"], 6, 16, wl.BUCKET_SORTED, ids, {i: 8 * (1 + i % 2) for i in range(6)})
+    _run(w, "gemm_glu_staged_256x256x64_w8")

@@ -1,11 +1,13 @@
 """GPU parity of every selectable GEMM kernel variant (lora_set_tuning) against the CPU oracle: the
 automatic choice reaches only some of them at a given shape, the others stay reachable for tuning and must
 compute the same result.  Small workloads with a ragged last tile, packed and single calls."""
+import numpy as np
 import pytest
 
 from gpu_util import run_and_check
 from paper_2602_24044_amd import binding as B
 from paper_2602_24044_amd import workloads as wl
+from paper_2602_24044_amd.runtime import Session
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +56,27 @@ def test_small_batch_tiles_and_their_edges(n_tokens, path):
     run_and_check(wl.qwen_decode(shrink=8, n_tokens=n_tokens), path=path)
     if n_tokens in (1, 33):
         run_and_check(wl.config2(shrink=2, n_tokens=n_tokens), path=path, packed=True)
+
+
+@pytest.mark.parametrize("n_tokens,cols,kernel", [
+    (1300, 4096, "gemm_fused_staged_128x256x64_w8"),        # 176 tiles: one round of two thirds of a 256 x 256 round
+    (2100, 4104, "gemm_fused_staged_256x192x64_w8"),        # ragged last column tile, ragged last row tile
+    (2049, 28680, "gemm_fused_staged_256x256x64_w8"),       # nine row tiles, the last with one row; XCD runs of unequal length
+    (257, 28672, "gemm_fused_staged_256x256x64_w8"),        # first size at which the staged tiles serve a small batch
+    (640, 28672, "gemm_fused_staged_256x192x64_w8"),
+])
+@pytest.mark.parametrize("mode", [wl.BUCKET_SORTED, wl.BUCKET_RUNS])
+def test_staged_tile_choice(n_tokens, cols, kernel, mode):
+    # a short K keeps the oracle quick: the choice depends on the tile counts (256 CUs); few runs of one adapter and rows without one
+    rng = np.random.default_rng(n_tokens)
+    ids = np.repeat(rng.integers(-1, 12, size=n_tokens // 9 + 1), 9)[:n_tokens].astype(np.int32)
+    w = wl.custom("staged_tiles", 3, [(128, cols)], ["p"], 12, 32, mode, ids, {i: 8 * (1 + i % 4) for i in range(12)})
+    sess = Session(w)
+    try:
+        sess.load(w.resident)
+        sess.bucket()
+        sess.forward(0)
+        assert kernel in B.lora_last_launches(sess.ctx), B.lora_last_launches(sess.ctx)
+    finally:
+        sess.close()
+    run_and_check(w)
