@@ -347,13 +347,17 @@ __device__ inline void park_v_share(uint16_t* sV, int q, u32x4 packed)
 // (DeviceView::row_loc: one value per resident adapter, so it also tells adapters apart; -1 or rank 0: backbone only).  sV: the windows' scaled
 // shrink results in LDS, window mb at sV + mb * kPieceRows * kVStageStride.
 // ---------------------------------------------------------------------------------------------------
+// `ready` is called once the first D items are on their way and before acc or sV are looked at.
 // GLU: the column blocks alternate between two projections of the same tokens (block 2 j: columns n_first + 32 j ..
 // of the first, block 2 j + 1: the same columns of the second), each with its own B (b_unit / b_unit2) and its own
 // shrink results (sV / sV2).
-template <int MB, int NB, int D, bool GLU = false>
+struct NothingToAwait {
+    __device__ inline void operator()() const {}
+};
+template <int MB, int NB, int D, bool GLU = false, typename Ready = NothingToAwait>
 __device__ inline void expand_windows(f32x16 (&acc)[MB][NB], const int (&slot)[MB], const int (&rank)[MB], int n_first,
                                       int N, const DeviceView& dv, size_t b_unit, const uint16_t* sV, size_t b_unit2 = 0,
-                                      const uint16_t* sV2 = nullptr)
+                                      const uint16_t* sV2 = nullptr, Ready&& ready = Ready{})
 {
     static_assert(!GLU || NB % 2 == 0, "pairs of column blocks");
     const int lane = threadIdx.x & (kWave - 1);
@@ -435,6 +439,7 @@ __device__ inline void expand_windows(f32x16 (&acc)[MB][NB], const int (&slot)[M
         q[d] = next_item();
         fetch(q[d], f[d]);
     }
+    ready();
     while (q[0].valid) {                                      // a pass without an item at position 0 has none at all
 #pragma unroll
         for (int d = 0; d < D; ++d) {

@@ -14,6 +14,8 @@ namespace lora {
 namespace {
 
 constexpr int kRT = 256;
+constexpr int kVB = 4;                   // shrink chunks per round of loads
+constexpr int kBDepth = 12;              // expand work items in flight
 constexpr int kVStride = kMaxRank + 8;   // bf16 elements per LDS row: 144 bytes, conflict-free 16-byte reads
 
 __global__ __launch_bounds__(kRT) void reduce_expand_kernel(ReduceArgs a)
@@ -36,26 +38,28 @@ __global__ __launch_bounds__(kRT) void reduce_expand_kernel(ReduceArgs a)
     const int n_first = (group * 4 - sl.blk0) * 32 + wave * 32;       // column inside the slice
 
     // The kernel is a chain of memory round trips; everything whose address is known at the start is requested
-    // at the start, oldest first what the next dependent load needs: this lane's row (slot, rank, token), the
-    // rank and scale of the row this thread stages, then the partial tiles.
-    const int my_slot[1] = {m_ok ? a.dv.row_loc[m] : -1};
-    const int my_rank[1] = {m_ok ? a.dv.row_rank[m] : 0};
-    const int my_tok = m_ok ? a.dv.perm[m] : 0;
+    // at the start, oldest first what the next dependent load needs: this lane's row (location, rank, token), the
+    // rank and scale of the row this thread stages, then the partial tiles, the shrink results and, as soon as the rows are
+    // there, the first B fragments, which so travel with the partial tiles.  No load is predicated (positions that do not
+    // exist read one that does and are dropped): behind a branch the compiler waits for all loads in flight.
+    const int mc = m_ok ? m : m_end - 1;
+    const int l_loc = a.dv.row_loc[mc], l_rank = a.dv.row_rank[mc], my_tok = a.dv.perm[mc];
     const int st_row = tid >> 3, st_seg = tid & 7;
     const int st_m = a.m_begin + win * kPieceRows + st_row;
     const bool st_on = st_m < m_end && st_seg * 8 < a.dv.max_rank;
-    const int st_rank = st_on ? a.dv.row_rank[st_m] : 0;
-    const float st_scale = st_on ? a.dv.row_scale[st_m] : 0.f;
+    const int st_mc = st_m < m_end ? st_m : m_end - 1;
+    const int st_rank = a.dv.row_rank[st_mc];
+    const float st_scale = a.dv.row_scale[st_mc];
 
-    f32x16 acc[1];
+    f32x16 acc[1][1];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
     // partial tiles are stored block by block in accumulator order (see the split-K GEMM): block
     // (window, n / 32) of split s is 1 KB-contiguous per register group, so these loads are fully
-    // coalesced; four splits (16 independent 16-byte loads per lane) are kept in flight
+    // coalesced; four splits (16 independent 16-byte loads per lane) are kept in flight.  Blocks behind the slice's last
+    // column exist too (slices are padded to 128 columns); what they hold is never stored.
     const int nblk = a.nblk;
     const int bn = group * 4 + wave;                                  // block in the packed partial matrix
-    const bool cols_on = n_first < N;
     f32x4 p[4][4];
     auto load_splits = [&](int s0) {
 #pragma unroll
@@ -73,52 +77,60 @@ __global__ __launch_bounds__(kRT) void reduce_expand_kernel(ReduceArgs a)
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[0][g * 4 + e] += p[ds][g][e];
+                    for (int e = 0; e < 4; ++e) acc[0][0][g * 4 + e] += p[ds][g][e];
             }
         }
     };
-    if (cols_on) load_splits(0);
-    // bias of the backbone layer (null: none), this lane's 16 columns
-    bf16x4 bias[4];
-    const bool bias_on = sl.bias != nullptr;
-    if (bias_on) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int n = n_first + g * 8 + h * 4;
-            bias[g] = __builtin_bit_cast(bf16x4, n < N ? *reinterpret_cast<const u32x2*>(sl.bias + n) : u32x2{0u, 0u});
-        }
-    }
-
-    // the window's shrink results, thread -> (row, 8 ranks): requested behind the first partial tiles, for every
-    // existing row whatever its rank (what lies beyond a row's rank was never written and is dropped below): the
-    // loads then do not wait for the row's rank to arrive, one memory round trip less on the kernel's chain
+    load_splits(0);
+    // the window's shrink results, thread -> (row, 8 ranks), whatever the row's rank (what lies beyond it was never
+    // written and is dropped below): the first kVB chunks now, further ones a round at a time
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-    if (st_on) {
-#pragma unroll 4
-        for (int c = 0; c < a.n_kc; ++c) {
-            const float* vp = sl.vpart + ((size_t)c * T + st_m) * a.dv.max_rank + st_seg * 8;
-            lo += *reinterpret_cast<const f32x4*>(vp);
-            hi += *reinterpret_cast<const f32x4*>(vp + 4);
+    f32x4 vl[kVB], vu[kVB];
+    auto load_chunks = [&](int c0) {
+#pragma unroll
+        for (int d = 0; d < kVB; ++d) {
+            const int c = c0 + d < a.n_kc ? c0 + d : c0;
+            const float* vp = sl.vpart + ((size_t)c * T + st_mc) * a.dv.max_rank + (st_on ? st_seg * 8 : 0);
+            vl[d] = *reinterpret_cast<const f32x4*>(vp);
+            vu[d] = *reinterpret_cast<const f32x4*>(vp + 4);
         }
-    }
+    };
+    auto add_chunks = [&](int c0) {
+#pragma unroll
+        for (int d = 0; d < kVB; ++d)
+            if (c0 + d < a.n_kc) {
+                lo += vl[d];
+                hi += vu[d];
+            }
+    };
+    load_chunks(0);
 
-    if (cols_on) {
+    const int my_slot[1] = {m_ok ? l_loc : -1};
+    const int my_rank[1] = {m_ok ? l_rank : 0};
+    // what comes behind the request for the first B fragments: the sums, the bias (null: none), the window's scaled shrink
+    // results as bf16 in LDS
+    auto sums = [&]() {
         add_splits(0);
+        add_chunks(0);
         for (int s0 = 4; s0 < a.split_k; s0 += 4) {
             load_splits(s0);
             add_splits(s0);
         }
-    }
-
-    if (bias_on) {
+        for (int c0 = kVB; c0 < a.n_kc; c0 += kVB) {
+            load_chunks(c0);
+            add_chunks(c0);
+        }
+        if (sl.bias != nullptr) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+            for (int g = 0; g < 4; ++g) {
+                const int n = n_first + g * 8 + h * 4;
+                if (n < N) {
+                    const bf16x4 b = __builtin_bit_cast(bf16x4, *reinterpret_cast<const u32x2*>(sl.bias + n));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[0][g * 4 + e] += (float)bias[g][e];
-    }
-
-    // stage the scaled shrink results as bf16
-    {
+                    for (int e = 0; e < 4; ++e) acc[0][0][g * 4 + e] += (float)b[e];
+                }
+            }
+        }
         u32x4 packed = {0u, 0u, 0u, 0u};
         if (st_on && st_seg * 8 < st_rank) {
             bf16x8 vb;
@@ -130,12 +142,9 @@ __global__ __launch_bounds__(kRT) void reduce_expand_kernel(ReduceArgs a)
             packed = __builtin_bit_cast(u32x4, vb);
         }
         *reinterpret_cast<u32x4*>(sV + st_row * kVStride + st_seg * 8) = packed;
-    }
-    __syncthreads();
-
-    f32x16 accw[1][1] = {{acc[0]}};
-    expand_windows<1, 1, 12>(accw, my_slot, my_rank, n_first, N, a.dv, sl.b_unit, sV);
-    acc[0] = accw[0][0];
+        __syncthreads();
+    };
+    expand_windows<1, 1, kBDepth>(acc, my_slot, my_rank, n_first, N, a.dv, sl.b_unit, sV, 0, nullptr, sums);
 
     if (m_ok) {
         uint16_t* orow = sl.out + (size_t)my_tok * N;
@@ -145,7 +154,7 @@ __global__ __launch_bounds__(kRT) void reduce_expand_kernel(ReduceArgs a)
             if (n < N) {
                 bf16x4 o;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[0][g * 4 + e];
+                for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[0][0][g * 4 + e];
                 *reinterpret_cast<u32x2*>(orow + n) = __builtin_bit_cast(u32x2, o);
             }
         }
