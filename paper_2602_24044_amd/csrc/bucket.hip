@@ -46,8 +46,9 @@ __device__ inline int block_excl_scan(int v, int* s_wave, int* total)
 }
 
 // Run-length encoding of row_slot[0..T); with align > 0 a run also ends at every multiple of align.  m_start /
-// m_slot (may be NULL): copies of the outputs in LDS for the next phase of the same workgroup.
-__device__ void rle(const int32_t* row_slot, int T, int align, int32_t* out_start, int32_t* out_slot,
+// m_slot (may be NULL): copies of the outputs in LDS for the next phase of the same workgroup.  Returns the number of
+// runs.
+__device__ int rle(const int32_t* row_slot, int T, int align, int32_t* out_start, int32_t* out_slot,
                     int32_t* out_n, int* s_wave, int* m_start, int* m_slot)
 {
     int running = 0;
@@ -75,12 +76,17 @@ __device__ void rle(const int32_t* row_slot, int T, int align, int32_t* out_star
         if (m_start) m_start[running] = T;
         *out_n = running;
     }
+    return running;
 }
 
 // Steps of up to kFastT tokens keep every intermediate array in LDS (keys in registers, grouped slots, the
 // piece list, the slot tables): the kernel is a chain of dependent phases, and a phase that reads back from
 // global memory what the previous one wrote pays a memory round trip each time.
 constexpr int kFastT = 4096;
+// SORTED, scatter of a chunk of 1024 tokens: wave after wave (a barrier each) up to kSerialWaves waves and above kWaveKeys
+// keys, otherwise all waves at once from counts per (wave, key), four barriers.
+constexpr int kSerialWaves = 4;
+constexpr int kWaveKeys = 512;
 constexpr int kFastPieces = kFastT + kFastT / kPieceRows + 2;
 
 __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
@@ -93,6 +99,9 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
     __shared__ int s_rank[kMaxKeys];     // fast path: slot tables
     __shared__ int s_loc[kMaxKeys];
     __shared__ float s_scale[kMaxKeys];
+    // SORTED: tokens of a chunk per (wave, key).  Shares its place with the piece list, which comes later.
+    uint16_t* const s_wcnt = reinterpret_cast<uint16_t*>(s_pstart);
+    static_assert(sizeof(s_pstart) >= (size_t)kNW * kWaveKeys * 2, "counts fit the piece list");
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int T = a.T;
     const int nkeys = a.n_slots + 1;     // key = slot + 1, key 0 = backbone only
@@ -100,6 +109,13 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
     const bool fast = T <= kFastT;
     constexpr int kFastChunks = kFastT / kBT;
 
+    // adapter ids first: they travel with the slot tables
+    int idreg[kFastChunks];
+#pragma unroll
+    for (int c = 0; c < kFastChunks; ++c) {
+        const int t = c * kBT + tid;
+        idreg[c] = fast && t < T ? a.ids[t] : -1;
+    }
     for (int k = tid; k < nkeys; k += kBT) s_run[k] = 0;
     if (fast) {
         for (int k = tid; k < a.n_slots; k += kBT) {
@@ -115,8 +131,7 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
     int keyreg[kFastChunks];
 #pragma unroll
     for (int c = 0; c < kFastChunks; ++c) keyreg[c] = 0;
-    auto key_of = [&](int t) {
-        const int id = a.ids[t];
+    auto key_of = [&](int id) {
         int key = 0;
         if (id >= 0) {
             int s = -1;
@@ -130,7 +145,7 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
         for (int c = 0; c < kFastChunks; ++c) {
             const int t = c * kBT + tid;
             if (t < T) {
-                const int key = key_of(t);
+                const int key = key_of(idreg[c]);
                 keyreg[c] = key;
                 if (sorted) {
                     atomicAdd(&s_run[key], 1);
@@ -143,7 +158,7 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
         }
     } else {
         for (int t = tid; t < T; t += kBT) {
-            const int key = key_of(t);
+            const int key = key_of(a.ids[t]);
             if (sorted) {
                 a.tok_key[t] = key;
                 atomicAdd(&s_run[key], 1);
@@ -193,6 +208,30 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
             const int cw = __popcll(peers);
             const int rem = T - c;
             const int nw = rem >= kBT ? kNW : (rem + kWave - 1) / kWave;
+            if (nw > kSerialWaves && nkeys <= kWaveKeys) {
+                // all waves at once: tokens per (wave, key), the waves in front of each summed per key
+                for (int k = tid; k < nw * kWaveKeys; k += kBT) s_wcnt[k] = 0;
+                __syncthreads();
+                if (valid && rank == cw - 1) s_wcnt[wave * kWaveKeys + key] = (uint16_t)cw;
+                __syncthreads();
+                int in_chunk = 0;
+                if (tid < nkeys)
+                    for (int w = 0; w < nw; ++w) {
+                        const int n = s_wcnt[w * kWaveKeys + tid];
+                        s_wcnt[w * kWaveKeys + tid] = (uint16_t)in_chunk;
+                        in_chunk += n;
+                    }
+                __syncthreads();
+                if (valid) {
+                    const int pos = s_run[key] + s_wcnt[wave * kWaveKeys + key] + rank;
+                    a.perm[pos] = t;
+                    a.row_slot[pos] = key - 1;
+                    if (fast) s_row[pos] = key - 1;
+                }
+                __syncthreads();
+                if (tid < nkeys) s_run[tid] += in_chunk;
+                continue;
+            }
             for (int w = 0; w < nw; ++w) {
                 if (wave == w && valid) {
                     const int pos = s_run[key] + rank;
@@ -224,12 +263,11 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
     }
 
     rle(rs, T, 0, a.seg_start, a.seg_slot, a.n_seg, s_wave, nullptr, nullptr);
-    rle(rs, T, kPieceRows, a.piece_start, a.piece_slot, a.n_pieces, s_wave, fast ? s_pstart : nullptr,
+    const int n_pieces = rle(rs, T, kPieceRows, a.piece_start, a.piece_slot, a.n_pieces, s_wave, fast ? s_pstart : nullptr,
         fast ? s_pslot : nullptr);
     __syncthreads();
 
     // one 16-byte record per piece for the shrink work loop
-    const int n_pieces = *a.n_pieces;
     for (int p = tid; p < n_pieces; p += kBT) {
         int begin, end, s, r, loc;
         if (fast) {
