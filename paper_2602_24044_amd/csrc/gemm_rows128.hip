@@ -223,13 +223,19 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
         if (front == 0) prefetch_v_issue(pre, a, sl, m0 + wm * WTM);      // else: not there yet
     }
     // Shrink inside the launch: the tile workgroups need its results only in the epilogue.  The counter of the
-    // shrink workgroups is polled four tiles before the end (a copy into LDS, ordered like the tile copies: it
-    // has landed when tile nk - 2 has); two tiles before the end one thread reads the verdict, makes the shrink
-    // results visible and publishes it; during the last tile every wave requests its shares of the results.
-    // When the poll came too early the wait after the loop takes over.
+    // shrink workgroups is polled kPollTile tiles before the end (wave 0 copies it into LDS); two tiles before the end
+    // one thread reads the verdict, makes the shrink results visible and publishes it; during the last tile every wave
+    // requests its shares of the results.  When the poll came too early the wait after the loop takes over.
+    // The verdict needs the poll in LDS.  Copies land in the order in which a wave requests them, and in front of tile
+    // nk - 2 a wave waits for everything but the copies of tile nk - 1.  Those are requested while tile nk - NS is
+    // multiplied, that is behind the poll with up to kPollTile stages.  With more stages (or where the first copies
+    // already reach tile nk - 1) the poll is the youngest request, and wave 0 waits for all of them there.
+    constexpr int kPollTile = 4;
+    constexpr bool kPollYoungest = NS > kPollTile;
     bool early = false;
-    const bool poll_on = PRE && front > 0 && nk >= 4;
+    const bool poll_on = PRE && front > 0 && nk >= kPollTile;
     const uint32_t poll_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)s_poll;
+    if (PRE && front > 0 && tid == 0) s_poll[0] = 0u;        // a word that has not landed reads as "not yet"
     // Past the wait for the shrink workgroups every tile workgroup takes a ticket; the one with the last ticket
     // sets the two counters back to zero for the next launch (at the end of the kernel: nobody of this launch
     // looks at them any more).  The ticket is requested here and read only then, so that nobody waits for it.
@@ -255,6 +261,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     auto wait_for_tile = [&](int t) {
         int young = nk - 1 - t;
         if (young > NS - 2) young = NS - 2;
+        if (kPollYoungest && poll_on && wave == 0 && t == nk - 2) young = 0;      // the poll has to land too
         if (young >= 5) wait_copies_then_barrier<(NS >= 7 ? 5 : 0) * QPT>();
         else if (young == 4) wait_copies_then_barrier<(NS >= 6 ? 4 : 0) * QPT>();
         else if (young == 3) wait_copies_then_barrier<(NS >= 5 ? 3 : 0) * QPT>();
@@ -266,9 +273,9 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     auto behind_barrier = [&](int t) {
         if constexpr (PRE) {
             if (poll_on) {
-                if (t == nk - 4 && wave == 0) poll4_to_lds(a.sync, __builtin_amdgcn_readfirstlane(poll_addr));
+                if (t == nk - kPollTile && wave == 0) poll4_to_lds(a.sync, __builtin_amdgcn_readfirstlane(poll_addr));
                 if (t == nk - 2 && threadIdx.x == 0) {
-                    const bool done = s_poll[0] >= (uint32_t)a.front_expect;     // landed: older than the copies the wait let pass
+                    const bool done = s_poll[0] >= (uint32_t)a.front_expect;     // landed, see above
                     if (done) passed_the_wait();
                     s_early = done ? 1u : 0u;
                 }

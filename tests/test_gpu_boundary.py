@@ -124,3 +124,73 @@ def test_loads_on_a_copy_stream_between_steps_wait_for_this_contexts_forwards_on
     finally:
         A.close()
         Bs.close()
+
+
+def _late_shrink_workload(n_tokens):
+    """gate|up over a short K with an adapter of the largest rank per token: the launch's shrink workgroups have more to
+    do than its tile workgroups, which so arrive at their epilogue first."""
+    n_ad = min(n_tokens, 64)
+    ids = (np.arange(n_tokens) % n_ad).astype(np.int32)
+    return wl.custom("late_shrink", 41 + n_tokens, [(512, 1792), (512, 1792)], ["gate", "up"], n_ad, 64, wl.BUCKET_SORTED, ids,
+                     {i: 64 for i in range(n_ad)})
+
+
+SHRINK_INSIDE = [(1, "gemm_fused_32x128x64_w4"), (32, "gemm_fused_32x128x64_w4"), (33, "gemm_fused_64x128x64_w4"),
+                 (64, "gemm_fused_64x128x64_w4"), (300, "gemm_fused_128x128x64_w4")]
+
+
+@pytest.mark.parametrize("n_tokens,kernel", SHRINK_INSIDE)
+def test_tiles_wait_for_the_shrink_results_of_their_own_launch(n_tokens, kernel):
+    """Every second launch has NaN for x and so leaves NaN in the scratch of the shrink results: a tile workgroup that
+    passes the wait before this launch's results are there carries them into its output."""
+    w = _late_shrink_workload(n_tokens)
+    announce(f"wait inside the launch: T={n_tokens} {kernel}")
+    sess = Session(w, path=B.LORA_PATH_FUSED)
+    try:
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_INLINE_SHRINK, B.LORA_INLINE_SHRINK_ON)
+        sess.load(w.resident)
+        sess.bucket()
+        x_nan = [torch.full_like(t, float("nan")) for t in sess.x]
+        x_ok = sess.x
+        outs = []
+        for rep in range(40):
+            sess.x = x_nan if rep % 2 == 0 else x_ok
+            sess.forward_group([0, 1])
+            assert B.lora_last_launches(sess.ctx) == [kernel]
+            if rep % 2:
+                outs.append([o.clone() for o in sess.out])
+        torch.cuda.synchronize()
+        sess.x = x_ok
+        _check_all(sess, w)
+        for k, out in enumerate(outs):
+            for p in range(len(w.proj)):
+                assert torch.equal(out[p], sess.out[p]), (k, p)
+        assert B.lora_poll_device_flags(sess.ctx) == (B.LORA_OK, 0)
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("n_tokens,kernel", SHRINK_INSIDE)
+def test_expired_wait_in_the_automatic_tiles(n_tokens, kernel):
+    w = _late_shrink_workload(n_tokens)
+    announce(f"expired wait: T={n_tokens} {kernel}")
+    sess = Session(w, path=B.LORA_PATH_FUSED)
+    try:
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_INLINE_SHRINK, B.LORA_INLINE_SHRINK_ON)
+        sess.load(w.resident)
+        sess.bucket()
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_SHRINK_WAIT_TEST, 1)
+        sess.forward_group([0, 1])
+        assert B.lora_last_launches(sess.ctx) == [kernel]
+        torch.cuda.synchronize()
+        with pytest.raises(B.LoraError) as e:
+            B.lora_poll_device_flags(sess.ctx)
+        assert e.value.status == B.LORA_ERR_HIP
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_SHRINK_WAIT_TEST, 0)
+        sess.forward_group([0, 1])
+        assert B.lora_last_launches(sess.ctx) == ["shrink", kernel]
+        torch.cuda.synchronize()
+        _check_all(sess, w)
+        assert B.lora_poll_device_flags(sess.ctx) == (B.LORA_OK, 0)
+    finally:
+        sess.close()
