@@ -84,7 +84,7 @@ __device__ int rle(const int32_t* row_slot, int T, int align, int32_t* out_start
 // global memory what the previous one wrote pays a memory round trip each time.
 constexpr int kFastT = 4096;
 // SORTED, scatter of a chunk of 1024 tokens: wave after wave (a barrier each) up to kSerialWaves waves and above kWaveKeys
-// keys, otherwise all waves at once from counts per (wave, key), four barriers.
+// keys, otherwise all waves at once from counts per (wave, key), five barriers.
 constexpr int kSerialWaves = 4;
 constexpr int kWaveKeys = 512;
 constexpr int kFastPieces = kFastT + kFastT / kPieceRows + 2;
@@ -230,6 +230,7 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
                 }
                 __syncthreads();
                 if (tid < nkeys) s_run[tid] += in_chunk;
+                __syncthreads();                              // the next chunk may place its first wave at once
                 continue;
             }
             for (int w = 0; w < nw; ++w) {

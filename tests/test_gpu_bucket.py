@@ -96,3 +96,24 @@ def test_runs_map_over_several_workgroups_with_runs_across_their_boundaries():
         assert check_segments(sess, w) == oracle.FLAG_NOT_RESIDENT
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("T,n_slots", [(1025, 64), (1100, 100), (1280, 300), (2049, 511), (2100, 128), (3328, 511), (4097, 300), (5200, 300),
+                                       # last chunk of five waves, and more keys than the counts per (wave, key) hold
+                                       (2369, 200), (2100, 512)])
+def test_sorted_map_whose_last_chunk_is_placed_wave_after_wave(T, n_slots):
+    # full chunks of 1024 tokens are placed by all waves at once, a last one of up to 256 tokens wave after wave; the
+    # offsets of keys from 64 on are carried over by other waves than the first
+    w = _bucket_only_workload(T, n_slots, 50 + T, wl.BUCKET_SORTED)
+    announce(f"bucket T={T} n_slots={n_slots}")
+    sess = Session(w, upload_inputs=False)
+    try:
+        order = np.random.default_rng(T).permutation(n_slots)
+        sess.load(list(range(n_slots)), slots=[int(s) for s in order])
+        rng = np.random.default_rng(T + 1)
+        for rep in range(6):                              # other ids each time: a position that is not written keeps an old one
+            w.token_ids = rng.permutation(w.token_ids)
+            sess.bucket(torch.from_numpy(w.token_ids).to(sess.device))
+            assert check_segments(sess, w) == 0
+    finally:
+        sess.close()
