@@ -97,6 +97,11 @@ void fused_tile(int fv, int& bm, int& bn)
     bn = fv == 10 ? 256 : (fv == 11 ? 192 : 128);
 }
 
+// The 32-wide-K kernels and the register-staged ones address x and W with 32-bit byte offsets, the 64-wide-K kernels
+// with 32-bit element offsets: an operand of 4 GiB or more takes the latter.
+bool over_byte_offsets(uint64_t rows, int K) { return rows * (uint64_t)K >= (1ull << 31); }
+bool fused_wide_k(int fv) { return (fv >= 8 && fv <= 11) || fv == 13 || fv == 14 || fused_small(fv); }
+
 // Device-visible address of a pointer into pinned (page-locked, mapped) host memory, or NULL when the pointer
 // is anything else (pageable host memory must never reach a kernel).
 const void* device_view_of_pinned(const void* p)
@@ -427,6 +432,7 @@ lora_status plan_forward(const lora_ctx* c, int32_t T, int32_t n, const int32_t*
         // and up to 128 tokens a 256-row tile would copy and multiply rows that do not exist
         if (split_variant == 0)
             split_variant = T <= 32 ? kSplit32 : T <= 64 ? kSplit64 : (T <= 128 || n_pad_total <= 2048 || (n_pad_total <= 4096 && K <= 8192 && T <= 256)) ? 7 : 6;
+        if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)n_max, K)) && !split_wide_k(split_variant)) split_variant = 6;
         const int bm = split_bm(split_variant), bn = split_variant == 2 ? 64 : 128;
         const long tiles = tiles_of(bm, bn);
         // The 64-wide-K kernels give a quarter of the CUs workgroups that only shrink, from the start (a shrink
@@ -1207,6 +1213,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                 if (T > 256 && (fv == 10 || fv == 11) && staged != 3) fv = staged;
             }
         }
+        if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)plan.n_max, K)) && !fused_wide_k(fv)) fv = glu ? 8 : 10;
         const bool use_tail = auto_variant && fv == 0 && m_full < T;
         const int m_split = use_tail ? m_full : T;
         // Small batches leave CUs without a tile (224 tiles of 256 x 128 for a Llama-8B gate|up, 198 of 256 x 192
@@ -1258,7 +1265,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             // 8 .. 11, 13, 14, 20 .. 23: 64-wide K tiles through the copy instruction; 12: the 32-wide 256 x 256 eight-wave kernel
             const int wide = fused_small(fv) ? fv - kFused32 + 6 : fv >= 13 ? fv - 9 : fv - 8;
             const hipError_t le = glu ? (fv == 0 ? launch_gemm_staged_glu(a, s, &name) : launch_gemm_rows128_glu(a, sa, wide, s, &name))
-                                  : ((fv >= 8 && fv <= 11) || fv == 13 || fv == 14 || fused_small(fv))
+                                  : fused_wide_k(fv)
                                       ? launch_gemm_rows128_fused(a, sa, wide, s, &name)
                                       // 0 (the big tile of the automatic choice), 15, 16: tiles staged through registers
                                       : (fv == 0 || (fv >= 15 && fv <= 18) || fv == kStaged192 || fv == kStaged128)

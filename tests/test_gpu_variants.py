@@ -3,6 +3,7 @@ automatic choice reaches only some of them at a given shape, the others stay rea
 compute the same result.  Small workloads with a ragged last tile, packed and single calls."""
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import run_and_check
 from paper_2602_24044_amd import binding as B
@@ -80,3 +81,58 @@ def test_staged_tile_choice(n_tokens, cols, kernel, mode):
     finally:
         sess.close()
     run_and_check(w)
+
+
+def _large_operand(T, K, cols, gated=False, tuning=None):
+    """One call without adapters on operands of 4 GiB, compared with the fp32 product at the rows and columns around
+    byte 2^32 of x and W, at the ends and at random places."""
+    dev = torch.device("cuda:0")
+    n = 2 if gated else 1
+    cfg = B.make_config([(K, cols)] * n, 1, 8, T, 1)
+    nbytes = B.lora_slab_bytes(cfg)
+    slab = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    cfg.slab, cfg.slab_bytes = slab.data_ptr(), nbytes
+    ctx = B.lora_create(cfg)
+    try:
+        for key, value in (tuning or {}).items():
+            B.lora_set_tuning(ctx, key, value)
+        gen = torch.Generator(device=dev).manual_seed(T + cols)
+        x = torch.empty((T, K), dtype=torch.bfloat16, device=dev).normal_(generator=gen)
+        W = [torch.empty((cols, K), dtype=torch.bfloat16, device=dev).normal_(0.0, 0.02, generator=gen) for _ in range(n)]
+        y = torch.empty((T, cols), dtype=torch.bfloat16, device=dev)
+        ids = torch.full((T,), -1, dtype=torch.int32, device=dev)
+        st = torch.cuda.current_stream().cuda_stream
+        seg = B.lora_bucket(ctx, ids.data_ptr(), T, B.LORA_BUCKET_RUNS, st)
+        if gated:
+            B.lora_layer_forward_glu(ctx, 0, 1, x.data_ptr(), W[0].data_ptr(), W[1].data_ptr(), seg, y.data_ptr(), st)
+        else:
+            B.lora_layer_forward(ctx, 0, x.data_ptr(), W[0].data_ptr(), seg, y.data_ptr(), st)
+        print(f"[gpu-case] T={T} K={K} cols={cols} {B.lora_last_launches(ctx)}", flush=True)
+        edge = 2 ** 31 // K
+        rng = np.random.default_rng(1)
+
+        def picks(size):
+            return sorted({i for i in [0, 1, 2, 3, edge - 1, edge, edge + 1, edge + 2, edge + 3, size - 2, size - 1, *rng.integers(0, size, 40)] if i < size})
+
+        r, c = torch.tensor(picks(T), device=dev), torch.tensor(picks(cols), device=dev)
+        ref = [x[r].float() @ m[c].float().t().contiguous() for m in W]
+        ref = torch.nn.functional.silu(ref[0]) * ref[1] if gated else ref[0]
+        got = y[r][:, c].float()
+        assert float((got - ref).abs().max() / ref.abs().max()) <= 5e-3
+    finally:
+        B.lora_destroy(ctx)
+
+
+@pytest.mark.parametrize("T", [257, 1100])
+@pytest.mark.parametrize("gated", [False, True])
+def test_weights_of_4_gib(T, gated):
+    _large_operand(T, 16384, 131080, gated)
+
+
+@pytest.mark.parametrize("tuning", [{}, {B.LORA_TUNE_FUSED_VARIANT: B.FUSED_VARIANTS["256x128x32_w8"]}])
+def test_activations_of_4_gib(tuning):
+    _large_operand(200003, 16384, 200, tuning=tuning)
+
+
+def test_weights_of_4_gib_in_an_explicit_split_variant():
+    _large_operand(100, 2 ** 21, 1032, tuning={B.LORA_TUNE_SPLIT_VARIANT: B.SPLIT_VARIANTS["256x128x32_w4"]})
