@@ -90,6 +90,7 @@ constexpr int kFused32 = 20, kFused64 = 21, kFusedPair32 = 22, kFusedPair64 = 23
 constexpr int kGlu128W8 = 24;                // gate and up, 128 x 128 with eight waves
 bool fused_small(int fv) { return fv >= kFused32 && fv <= kGlu128W8; }
 bool fused_pair(int fv) { return fv == kFusedPair32 || fv == kFusedPair64; }
+constexpr long kMinFrontCus = 8;             // CUs without a tile from which on the shrink can run inside the launch
 // tile of the 64-wide-K fused variants that can shrink inside the launch
 void fused_tile(int fv, int& bm, int& bn)
 {
@@ -1209,8 +1210,13 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                 // From 257 tokens on a launch that wants the wide tiles is bound by the matrix cores: the staged tiles,
                 // although their shrink is a launch of its own (Llama-8B gate|up: 400 tokens 158 -> 141 + 9 us, 640 tokens
                 // 245 -> 196, 777 tokens 278 -> 248, 1024 tokens 294 -> 259).  The narrower ones stay: q|k|v and o at 640 -
-                // 1024 tokens 60 and 56 us against 71 and 64.
-                if (T > 256 && (fv == 10 || fv == 11) && staged != 3) fv = staged;
+                // 1024 tokens 60 and 56 us against 71 and 64.  LORA_INLINE_SHRINK_ON asks for the shrink inside the launch
+                // wherever tiles leave CUs for it: the staged tiles cannot, so such a call keeps the copied ones.
+                int bm, bn;
+                fused_tile(fv, bm, bn);
+                const bool inside = c->tune[LORA_TUNE_INLINE_SHRINK] == LORA_INLINE_SHRINK_ON && !c->inline_shrink_off &&
+                                    c->n_cus - tiles_of(bm, bn) >= kMinFrontCus;
+                if (T > 256 && (fv == 10 || fv == 11) && staged != 3 && !inside) fv = staged;
             }
         }
         if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)plan.n_max, K)) && !fused_wide_k(fv)) fv = glu ? 8 : 10;
@@ -1230,7 +1236,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             const int chunks = std::max(1, std::min<int>(kMaxShrinkChunks, K / 4096));
             const long pieces = (long)n * std::min<long>(T, (long)c->n_resident + (T + kPieceRows - 1) / kPieceRows);
             const double t_main = (double)(bm + bn) * K * 2.0 / 48e3;                   // us, see plan_forward
-            if (idle >= 8 && chunks <= n_kc &&      // the scratch for the shrink results is sized for n_kc chunks
+            if (idle >= kMinFrontCus && chunks <= n_kc &&      // the scratch for the shrink results is sized for n_kc chunks
                 (c->tune[LORA_TUNE_INLINE_SHRINK] == LORA_INLINE_SHRINK_ON ||
                  (double)(pieces * chunks) * (4.0 * (K / chunks) / 2048.0) / (double)std::min<long>(idle, c->n_cus / 4) <= 0.6 * t_main)) {
                 front = (int)std::min<long>(idle, c->n_cus / 4);

@@ -15,6 +15,21 @@ pytestmark = pytest.mark.gpu
 FUSED_VARIANTS = sorted(B.FUSED_VARIANTS.values())
 SPLIT_VARIANTS = sorted(B.SPLIT_VARIANTS.values())
 
+
+def _launches(w, tuning=None, path=B.LORA_PATH_AUTO):
+    """Names of the launches of projection 0."""
+    sess = Session(w, path=path)
+    try:
+        for key, value in (tuning or {}).items():
+            B.lora_set_tuning(sess.ctx, key, value)
+        sess.load(w.resident)
+        sess.bucket()
+        sess.forward(0)
+        return B.lora_last_launches(sess.ctx)
+    finally:
+        sess.close()
+
+
 @pytest.mark.parametrize("variant", FUSED_VARIANTS)
 def test_fused_variant_decode_and_prefill(variant):
     tuning = {B.LORA_TUNE_FUSED_VARIANT: variant}
@@ -136,3 +151,14 @@ def test_activations_of_4_gib(tuning):
 
 def test_weights_of_4_gib_in_an_explicit_split_variant():
     _large_operand(100, 2 ** 21, 1032, tuning={B.LORA_TUNE_SPLIT_VARIANT: B.SPLIT_VARIANTS["256x128x32_w4"]})
+
+
+@pytest.mark.parametrize("mode,launches", [(B.LORA_INLINE_SHRINK_ON, ["gemm_fused_256x256x64_w8"]),
+                                           (B.LORA_INLINE_SHRINK_AUTO, ["shrink", "gemm_fused_staged_256x256x64_w8"])])
+def test_shrink_inside_a_wide_launch_of_more_than_256_tokens(mode, launches):
+    # 224 tiles of 256 x 256: 32 CUs without a tile
+    ids = np.random.default_rng(9).integers(-1, 6, size=400).astype(np.int32)
+    w = wl.custom("wide_inline", 9, [(128, 28672)], ["p"], 6, 16, wl.BUCKET_SORTED, ids, {i: 8 * (1 + i % 2) for i in range(6)})
+    tuning = {B.LORA_TUNE_INLINE_SHRINK: mode}
+    assert _launches(w, tuning) == launches
+    run_and_check(w, tuning=tuning)
