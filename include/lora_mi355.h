@@ -342,7 +342,13 @@ enum {
     LORA_FUSED_256x256x64_W4 = 14,
     LORA_FUSED_STAGED_256x256x64_W8 = 15, /* tiles staged through registers (ordinary loads, LDS writes), two LDS stages:
                                              what LORA_FUSED_AUTO takes above 1024 tokens when the grid fills the chip */
-    LORA_FUSED_STAGED_256x256x64_W4 = 16
+    LORA_FUSED_STAGED_256x256x64_W4 = 16,
+    LORA_FUSED_32x128x64_W4 = 20,         /* what LORA_FUSED_AUTO takes up to 32 and up to 64 tokens; PAIR: two workgroups */
+    LORA_FUSED_64x128x64_W4 = 21,         /* per CU, where there are more tiles than CUs */
+    LORA_FUSED_32x128x64_W4_PAIR = 22,
+    LORA_FUSED_64x128x64_W4_PAIR = 23,
+    LORA_FUSED_STAGED_256x192x64_W8 = 30, /* smaller staged tiles, for grids that would leave the last round of the */
+    LORA_FUSED_STAGED_128x256x64_W8 = 31  /* 256 x 256 ones mostly empty */
 };
 /* Values of LORA_TUNE_SPLIT_VARIANT. */
 enum {
@@ -354,7 +360,9 @@ enum {
     LORA_SPLIT_256x128x64_W8 = 6,
     LORA_SPLIT_128x128x64_W4 = 7,
     LORA_SPLIT_256x128x32_W8 = 8,
-    LORA_SPLIT_256x128x64_W4 = 9
+    LORA_SPLIT_256x128x64_W4 = 9,
+    LORA_SPLIT_32x128x64_W4 = 10,         /* what LORA_SPLIT_AUTO takes up to 32 and up to 64 tokens */
+    LORA_SPLIT_64x128x64_W4 = 11
 };
 lora_status lora_set_tuning(lora_ctx *ctx, int32_t key, int32_t value);
 

@@ -75,20 +75,20 @@ struct Layout {
 };
 
 // Rows of the split-K GEMM variants' tiles.  6, 7, 9 and the small-batch variants 10 and 11 walk K in 64-wide tiles.
-constexpr int kSplit32 = 10, kSplit64 = 11;
+constexpr int kSplit32 = LORA_SPLIT_32x128x64_W4, kSplit64 = LORA_SPLIT_64x128x64_W4;
 int split_bm(int variant)
 {
     if (variant == kSplit32) return 32;
     if (variant == kSplit64) return 64;
     return (variant == 3 || variant == 4 || variant == 7) ? 128 : 256;
 }
-bool split_wide_k(int variant) { return variant == 6 || variant == 7 || variant >= 9; }
+bool split_wide_k(int variant) { return variant == 6 || variant == 7 || (variant >= 9 && variant <= kSplit64); }
 
-// Variants of the 64-wide-K fused GEMM that only the automatic choice takes: 32- and 64-row tiles, one workgroup per
-// CU or (kFusedPair*) two.
-constexpr int kFused32 = 20, kFused64 = 21, kFusedPair32 = 22, kFusedPair64 = 23;
-constexpr int kGlu128W8 = 24;                // gate and up, 128 x 128 with eight waves
-bool fused_small(int fv) { return fv >= kFused32 && fv <= kGlu128W8; }
+// Small-batch variants of the 64-wide-K fused GEMM: 32- and 64-row tiles, one workgroup per CU or (kFusedPair*) two.
+constexpr int kFused32 = LORA_FUSED_32x128x64_W4, kFused64 = LORA_FUSED_64x128x64_W4,
+              kFusedPair32 = LORA_FUSED_32x128x64_W4_PAIR, kFusedPair64 = LORA_FUSED_64x128x64_W4_PAIR;
+constexpr int kGlu128W8 = kFusedPair64 + 1;  // gated call only: 128 x 128 with eight waves
+bool fused_small(int fv) { return fv >= kFused32 && fv <= kFusedPair64; }
 bool fused_pair(int fv) { return fv == kFusedPair32 || fv == kFusedPair64; }
 constexpr long kMinFrontCus = 8;             // CUs without a tile from which on the shrink can run inside the launch
 // tile of the 64-wide-K fused variants that can shrink inside the launch
@@ -101,7 +101,7 @@ void fused_tile(int fv, int& bm, int& bn)
 // The 32-wide-K kernels and the register-staged ones address x and W with 32-bit byte offsets, the 64-wide-K kernels
 // with 32-bit element offsets: an operand of 4 GiB or more takes the latter.
 bool over_byte_offsets(uint64_t rows, int K) { return rows * (uint64_t)K >= (1ull << 31); }
-bool fused_wide_k(int fv) { return (fv >= 8 && fv <= 11) || fv == 13 || fv == 14 || fused_small(fv); }
+bool fused_wide_k(int fv, bool glu) { return (fv >= 8 && fv <= 11) || fv == 13 || fv == 14 || fused_small(fv) || (glu && fv == kGlu128W8); }
 
 // Device-visible address of a pointer into pinned (page-locked, mapped) host memory, or NULL when the pointer
 // is anything else (pageable host memory must never reach a kernel).
@@ -142,7 +142,7 @@ int auto_split_cap(int N, int n_cus)
 // tokens) fills the chip better with smaller ones.  Llama-8B, 256 x 256 tiles -> this choice: 2100 tokens o 120 -> 94 us,
 // down 351 -> 281; 1300 tokens (before: 256 x 128 tiles of the 32-wide kernel) o 80 -> 73, down 232 -> 216, q|k|v 120 -> 94.
 // tail: cost of 256 x 256 tiles when the rows behind the full rounds go to the split-K path (0: they do not).
-constexpr int kStaged192 = 30, kStaged128 = 31;
+constexpr int kStaged192 = LORA_FUSED_STAGED_256x192x64_W8, kStaged128 = LORA_FUSED_STAGED_128x256x64_W8;
 template <typename TilesOf>
 int pick_fused_variant(int n_cus, TilesOf&& tiles_of, double tail)
 {
@@ -1219,14 +1219,14 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                 if (T > 256 && (fv == 10 || fv == 11) && staged != 3 && !inside) fv = staged;
             }
         }
-        if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)plan.n_max, K)) && !fused_wide_k(fv)) fv = glu ? 8 : 10;
+        if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)plan.n_max, K)) && !fused_wide_k(fv, glu)) fv = glu ? 8 : 10;
         const bool use_tail = auto_variant && fv == 0 && m_full < T;
         const int m_split = use_tail ? m_full : T;
         // Small batches leave CUs without a tile (224 tiles of 256 x 128 for a Llama-8B gate|up, 198 of 256 x 192
         // for Qwen2.5-7B).  When those CUs can finish the shrink well inside the time the tiles stream, they do
         // it as the first workgroups of the GEMM launch and the separate shrink launch goes.
         int front = 0;
-        if (sa.on && ((fv >= 8 && fv <= 11) || fused_small(fv)) && T <= kSplitMaxTokens && m_split == T && !c->inline_shrink_off &&
+        if (sa.on && fused_wide_k(fv, glu) && fv != 13 && fv != 14 && T <= kSplitMaxTokens && m_split == T && !c->inline_shrink_off &&
             c->tune[LORA_TUNE_INLINE_SHRINK] != LORA_INLINE_SHRINK_OFF) {
             int bm, bn;
             fused_tile(fv, bm, bn);
@@ -1269,9 +1269,9 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             // rows of W a multiple of 4 KB apart, one row tile
             a.k_rot = T <= 128 && K % 2048 == 0 ? 1 : 0;
             // 8 .. 11, 13, 14, 20 .. 23: 64-wide K tiles through the copy instruction; 12: the 32-wide 256 x 256 eight-wave kernel
-            const int wide = fused_small(fv) ? fv - kFused32 + 6 : fv >= 13 ? fv - 9 : fv - 8;
+            const int wide = fv >= kFused32 ? fv - kFused32 + 6 : fv >= 13 ? fv - 9 : fv - 8;
             const hipError_t le = glu ? (fv == 0 ? launch_gemm_staged_glu(a, s, &name) : launch_gemm_rows128_glu(a, sa, wide, s, &name))
-                                  : fused_wide_k(fv)
+                                  : fused_wide_k(fv, false)
                                       ? launch_gemm_rows128_fused(a, sa, wide, s, &name)
                                       // 0 (the big tile of the automatic choice), 15, 16: tiles staged through registers
                                       : (fv == 0 || (fv >= 15 && fv <= 18) || fv == kStaged192 || fv == kStaged128)

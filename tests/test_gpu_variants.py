@@ -162,3 +162,44 @@ def test_shrink_inside_a_wide_launch_of_more_than_256_tokens(mode, launches):
     tuning = {B.LORA_TUNE_INLINE_SHRINK: mode}
     assert _launches(w, tuning) == launches
     run_and_check(w, tuning=tuning)
+
+
+@pytest.mark.parametrize("mode", [B.LORA_INLINE_SHRINK_OFF, B.LORA_INLINE_SHRINK_ON])
+@pytest.mark.parametrize("name", ["32x128x64_w4", "64x128x64_w4", "32x128x64_w4_pair", "64x128x64_w4_pair"])
+def test_shrink_inside_the_small_tiles(mode, name):
+    tuning = {B.LORA_TUNE_INLINE_SHRINK: mode, B.LORA_TUNE_FUSED_VARIANT: B.FUSED_VARIANTS[name]}
+    for n_tokens in (1, 33, 64):
+        w = wl.config2(shrink=8, n_tokens=n_tokens)
+        inside = mode == B.LORA_INLINE_SHRINK_ON
+        assert _launches(w, tuning, B.LORA_PATH_FUSED) == ([] if inside else ["shrink"]) + ["gemm_fused_" + name]
+        run_and_check(w, path=B.LORA_PATH_FUSED, tuning=tuning, packed=True)
+
+
+@pytest.mark.parametrize("mode", [B.LORA_INLINE_SHRINK_OFF, B.LORA_INLINE_SHRINK_ON])
+@pytest.mark.parametrize("n_tokens,kernel", [(1, "gemm_fused_32x128x64_w4_pair"), (32, "gemm_fused_32x128x64_w4_pair"),
+                                             (33, "gemm_fused_64x128x64_w4_pair"), (64, "gemm_fused_64x128x64_w4_pair"),
+                                             (65, "gemm_fused_128x128x64_w4")])
+def test_more_small_tiles_than_cus(n_tokens, kernel, mode):
+    # 258 column tiles of 128 for 256 CUs, the last one ragged; the 128-row tile leaves no CU for the shrink
+    ids = np.random.default_rng(n_tokens).integers(-1, 6, size=n_tokens).astype(np.int32)
+    w = wl.custom("pair_tiles", 11, [(320, 33000)], ["p"], 6, 16, wl.BUCKET_SORTED, ids, {i: 8 * (1 + i % 2) for i in range(6)})
+    tuning = {B.LORA_TUNE_INLINE_SHRINK: mode}
+    inside = mode == B.LORA_INLINE_SHRINK_ON and n_tokens <= 64
+    assert _launches(w, tuning) == ([] if inside else ["shrink"]) + [kernel]
+    run_and_check(w, tuning=tuning)
+
+
+@pytest.mark.parametrize("n_tokens,rows", [(1, 32), (31, 32), (32, 32), (33, 64), (63, 64), (64, 64), (65, 128)])
+def test_small_batch_tiles_by_name(n_tokens, rows):
+    w = wl.config2(shrink=8, n_tokens=n_tokens)
+    assert _launches(w, path=B.LORA_PATH_FUSED)[-1] == f"gemm_fused_{rows}x128x64_w4"
+    assert _launches(w, path=B.LORA_PATH_SPLITK) == [f"gemm_splitk_shrink_{rows}x128x64_w4", "reduce_expand"]
+
+
+@pytest.mark.parametrize("value", [24, 29, 32, 1000])
+def test_unknown_variants_fall_back(value):
+    w = wl.config2(shrink=8, n_tokens=100)
+    run_and_check(w, path=B.LORA_PATH_FUSED, tuning={B.LORA_TUNE_FUSED_VARIANT: value})
+    run_and_check(w, path=B.LORA_PATH_SPLITK, tuning={B.LORA_TUNE_SPLIT_VARIANT: value})
+    assert _launches(w, {B.LORA_TUNE_FUSED_VARIANT: value}, B.LORA_PATH_FUSED)[-1] == "gemm_fused_256x256_w8"
+    assert _launches(w, {B.LORA_TUNE_SPLIT_VARIANT: value}, B.LORA_PATH_SPLITK)[0] == "gemm_splitk_shrink_256x128_w8"
