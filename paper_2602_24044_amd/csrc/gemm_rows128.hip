@@ -55,7 +55,8 @@ __device__ inline void wait_copies_then_barrier()
 // stores silu(gate) * up.  A workgroup then owns BN / 2 output columns; the W part of a stage alternates between
 // the two matrices in blocks of 32 rows (block 2 j: rows of gate, block 2 j + 1: the same rows of up), so that a
 // wave holds both factors of every output element it owns in the same lane.
-template <int BM, int BN, int WGM, int WGN, bool FUSED, int NS, bool GLU = false>
+// ROT: an instance that can start its walk over K elsewhere (GemmArgs::k_rot, see below).
+template <int BM, int BN, int WGM, int WGN, bool FUSED, int NS, bool GLU = false, bool ROT = FUSED && BM <= 128>
 __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs a, ShrinkArgs sa)
 {
     static_assert(!GLU || FUSED, "the product is formed in the fused epilogue");
@@ -177,7 +178,6 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     // memory channels at a time: gate|up of Llama-8B (235 MB of W) at one token 66 -> 52 us, at 32 tokens 75 -> 61 (128-row
     // tiles).  Rows of 7 KB (K = 3584) do not need it (75 and 76 us), a 256-row tile gains nothing (step of 256 tokens
     // 231 us either way), and several row tiles lose by spreading over x (640 tokens, q|k|v: 60 -> 83 us).
-    constexpr bool ROT = FUSED && BM <= 128;
     const int rot = ROT && a.k_rot ? tile_n % nk : 0;
     const uint32_t cp_x = ring_addr + wave * XQ * 1024;
     const uint32_t cp_w = ring_addr + BM * kRowB + wave * WQ * 1024;
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool FUSED, int NS, bool GLU = false>
+template <int BM, int BN, int WGM, int WGN, bool FUSED, int NS, bool GLU = false, bool ROT = FUSED && BM <= 128>
 hipError_t launch_rows128(GemmArgs a, const ShrinkArgs& sa, hipStream_t stream)
 {
     a.tiles_m = (a.m_end - a.m_begin + BM - 1) / BM;
@@ -386,7 +386,7 @@ hipError_t launch_rows128(GemmArgs a, const ShrinkArgs& sa, hipStream_t stream)
     a.main_grid = grid;
     grid += extra;
     if (FUSED) grid += a.shrink_front;                    // those come first
-    hipLaunchKernelGGL((gemm_rows128_kernel<BM, BN, WGM, WGN, FUSED, NS, GLU>), dim3(grid), dim3(WGM * WGN * kWave), 0,
+    hipLaunchKernelGGL((gemm_rows128_kernel<BM, BN, WGM, WGN, FUSED, NS, GLU, ROT>), dim3(grid), dim3(WGM * WGN * kWave), 0,
                        stream, a, sa);
     return hipGetLastError();
 }
@@ -400,7 +400,10 @@ hipError_t launch_gemm_rows128_fused(const GemmArgs& a, const ShrinkArgs& none, 
     switch (variant) {
         case 1:
             *name = "gemm_fused_128x128x64_w4";
-            return launch_rows128<128, 128, 2, 2, true, 4>(a, none, stream);
+            // two instances: the one that can turn its walk costs a launch that does not 0.4 us (512 x 512 projection, 100
+            // tokens: 14.1 and 14.5 us)
+            if (a.k_rot) return launch_rows128<128, 128, 2, 2, true, 4, false, true>(a, none, stream);
+            return launch_rows128<128, 128, 2, 2, true, 4, false, false>(a, none, stream);
         case 2:
             *name = "gemm_fused_256x256x64_w8";
             return launch_rows128<256, 256, 2, 4, true, 2>(a, none, stream);

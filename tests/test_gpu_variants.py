@@ -203,3 +203,10 @@ def test_unknown_variants_fall_back(value):
     run_and_check(w, path=B.LORA_PATH_SPLITK, tuning={B.LORA_TUNE_SPLIT_VARIANT: value})
     assert _launches(w, {B.LORA_TUNE_FUSED_VARIANT: value}, B.LORA_PATH_FUSED)[-1] == "gemm_fused_256x256_w8"
     assert _launches(w, {B.LORA_TUNE_SPLIT_VARIANT: value}, B.LORA_PATH_SPLITK)[0] == "gemm_splitk_shrink_256x128_w8"
+
+
+@pytest.mark.parametrize("n_tokens", [65, 128])
+def test_turned_k_walk_of_the_128_row_tile(n_tokens):
+    # K of gate|up 2048: 32 K tiles, 112 column tiles; and a K that does not turn the walk, behind it on the same sizes
+    run_and_check(wl.config2(shrink=2, n_tokens=n_tokens), path=B.LORA_PATH_FUSED, packed=True)
+    run_and_check(wl.qwen_decode(shrink=2, n_tokens=n_tokens), path=B.LORA_PATH_FUSED, packed=True)
