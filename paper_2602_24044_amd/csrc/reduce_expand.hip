@@ -15,10 +15,15 @@ namespace {
 
 constexpr int kRT = 256;
 constexpr int kVB = 4;                   // shrink chunks per round of loads
-constexpr int kBDepth = 12;              // expand work items in flight
+// Expand work items in flight.  Their fragments travel beside the partial tiles, and with twelve the kernel needs 192
+// registers: two workgroups on a CU, so that 513 to 768 of them take a second round.  With eight it needs 157 and three fit.
+// Llama-8B, twelve -> eight: o at 640 tokens (640 workgroups) 15.8 -> 11.8 us, q|k|v at 512 tokens (768) 17.4 -> 13.3,
+// down at 256 tokens (256) 10.8 -> 9.7, q|k|v at 64 tokens of 16 adapters (96) 8.2 -> 8.3.
+constexpr int kBDepth = 8;
+constexpr int kPerCu = 3;                // workgroups on a CU, one wave each per SIMD
 constexpr int kVStride = kMaxRank + 8;   // bf16 elements per LDS row: 144 bytes, conflict-free 16-byte reads
 
-__global__ __launch_bounds__(kRT) void reduce_expand_kernel(ReduceArgs a)
+__global__ __launch_bounds__(kRT, kPerCu) void reduce_expand_kernel(ReduceArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint16_t sV[kPieceRows * kVStride];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
