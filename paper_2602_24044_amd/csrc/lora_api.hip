@@ -1152,11 +1152,20 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         auto small_variant = [&](int one, int pair, long tiles) { return tiles <= c->n_cus ? one : pair; };
         // gate and up with their product: the 64-wide-K kernel up to 1024 tokens (64-row tiles up to 64, 128-row tiles up
         // to 128, with eight waves where the tiles fill at least half the chip: Llama-8B, 99 tokens, 69 us with four, 66 with
-        // eight), the register-staged 256 x 256 tile above 1024 and, where its tiles fill three quarters of the chip, above 256
-        if (glu)
+        // eight), the register-staged 256 x 256 tile above.  It also serves 257 to 1024 tokens where its tiles fill three
+        // quarters of the chip and take half the rounds of the 256 x 128 ones, since a round of it costs more than one and a
+        // half of those.  Whole step, 256 x 128 -> 256 x 256, rounds in brackets: Llama-8B 400 tokens 328 -> 314 us (2, 1), 850
+        // tokens 609 -> 568 (4, 2), but 640 tokens 468 -> 497 (3, 2); Qwen2.5-7B 640 tokens 517 -> 487 (4, 2), but 340 tokens
+        // 380 -> 410 (3, 2) and 850 tokens 677 -> 689 (5, 3).
+        if (glu) {
+            auto rounds = [&](long tiles) { return (tiles + c->n_cus - 1) / c->n_cus; };
+            const long big = tiles_of(256, 256);
+            const bool staged = T > kSplitMaxTokens ||
+                                (T > 256 && big >= c->n_cus * 3 / 4 && 2 * rounds(big) <= rounds(tiles_of(256, 128)));
             fv = T <= 64    ? small_variant(kFused64, kFusedPair64, tiles_of(64, 128))
                  : T <= 128 ? (tiles_of(128, 128) >= c->n_cus / 2 ? kGlu128W8 : 9)
-                            : (T <= 256 || (T <= kSplitMaxTokens && tiles_of(256, 256) < c->n_cus * 3 / 4) ? 8 : 0);
+                            : (staged ? 0 : 8);
+        }
         // A last round of 256 x 256 tiles that fills less than half the chip costs as much as a full one.  When
         // the rows behind the full rounds are few enough for the split-K path, the fused launch can stop at the
         // full rounds and those rows take the split-K path (their shrink results are there already), which

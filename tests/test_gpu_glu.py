@@ -113,3 +113,15 @@ def test_staged_gated_tile_below_1025_tokens():
     ids = np.repeat(rng.integers(-1, 6, size=30), 10)[:261].astype(np.int32)
     w = wl.custom("glu_staged", 7, [(64, 14336), (64, 14336)], ["gate", "up"], 6, 16, wl.BUCKET_SORTED, ids, {i: 8 * (1 + i % 2) for i in range(6)})
     _run(w, "gemm_glu_staged_256x256x64_w8")
+
+
+@pytest.mark.parametrize("n_tokens,cols,kernel", [(520, 14336, "gemm_glu_256x128x64_w8"),        # 3 rounds of 256 x 128 tiles against 2
+                                                  (777, 14336, "gemm_glu_staged_256x256x64_w8"), # 4 against 2
+                                                  (300, 18944, "gemm_glu_256x128x64_w8"),        # 3 against 2
+                                                  (850, 18944, "gemm_glu_256x128x64_w8"),        # 5 against 3
+                                                  (1025, 18944, "gemm_glu_staged_256x256x64_w8")])
+def test_gated_tile_by_rounds(n_tokens, cols, kernel):
+    rng = np.random.default_rng(n_tokens)
+    ids = np.repeat(rng.integers(-1, 6, size=n_tokens // 10 + 1), 10)[:n_tokens].astype(np.int32)
+    w = wl.custom("glu_rounds", 8, [(64, cols), (64, cols)], ["gate", "up"], 6, 16, wl.BUCKET_SORTED, ids, {i: 8 * (1 + i % 2) for i in range(6)})
+    _run(w, kernel)
