@@ -235,7 +235,9 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     bool early = false;
     const bool poll_on = PRE && front > 0 && nk >= kPollTile;
     const uint32_t poll_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)s_poll;
-    if (PRE && front > 0 && tid == 0) s_poll[0] = 0u;        // a word that has not landed reads as "not yet"
+    if constexpr (PRE) {
+        if (front > 0 && tid == 0) s_poll[0] = 0u;           // a word that has not landed reads as "not yet"
+    }
     // Past the wait for the shrink workgroups every tile workgroup takes a ticket; the one with the last ticket
     // sets the two counters back to zero for the next launch (at the end of the kernel: nobody of this launch
     // looks at them any more).  The ticket is requested here and read only then, so that nobody waits for it.
@@ -261,7 +263,9 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     auto wait_for_tile = [&](int t) {
         int young = nk - 1 - t;
         if (young > NS - 2) young = NS - 2;
-        if (kPollYoungest && poll_on && wave == 0 && t == nk - 2) young = 0;      // the poll has to land too
+        if constexpr (PRE && kPollYoungest) {
+            if (poll_on && wave == 0 && t == nk - 2) young = 0;                   // the poll has to land too
+        }
         if (young >= 5) wait_copies_then_barrier<(NS >= 7 ? 5 : 0) * QPT>();
         else if (young == 4) wait_copies_then_barrier<(NS >= 6 ? 4 : 0) * QPT>();
         else if (young == 3) wait_copies_then_barrier<(NS >= 5 ? 3 : 0) * QPT>();
