@@ -142,6 +142,7 @@ int auto_split_cap(int N, int n_cus)
 // tokens) fills the chip better with smaller ones.  Llama-8B, 256 x 256 tiles -> this choice: 2100 tokens o 120 -> 94 us,
 // down 351 -> 281; 1300 tokens (before: 256 x 128 tiles of the 32-wide kernel) o 80 -> 73, down 232 -> 216, q|k|v 120 -> 94.
 // tail: cost of 256 x 256 tiles when the rows behind the full rounds go to the split-K path (0: they do not).
+constexpr double kRoundUs = 116.0 / 4096;    // a round of 256 x 256 tiles, per element of K
 constexpr int kStaged192 = LORA_FUSED_STAGED_256x192x64_W8, kStaged128 = LORA_FUSED_STAGED_128x256x64_W8;
 template <typename TilesOf>
 int pick_fused_variant(int n_cus, TilesOf&& tiles_of, double tail)
@@ -1187,11 +1188,17 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                     ts = std::min<long>(ts, std::max(1, (K / kBK) / 2));
                     ts = std::min<long>(ts, (long)(scr.part_elems / ((size_t)tail_pad * (size_t)n_pad_total)));
                     if (ts >= 2) {
-                        m_full = (int)(m_tiles_main * 256);
-                        tail_S = (int)ts;
-                        // the tail's two launches count as half a round of 256 x 256 tiles (measured: 0.54 for 340 rows of Llama-8B
-                        // q|k|v, 0.39 and 0.35 for 384 rows of Llama-70B o and down)
-                        tail_cost = (double)((m_tiles_main * tiles_n_big + c->n_cus - 1) / c->n_cus) + 0.5;
+                        // in rounds of 256 x 256 tiles (kRoundUs); the tail by the split-K cost model of plan_forward, 8 us for its
+                        // second launch.  Model and measured: 340 rows of Llama-8B q|k|v 0.57 and 0.54, 384 rows of Llama-70B o and
+                        // down 0.37 and 0.43, 0.31 and 0.33.
+                        const double tail_us = 384.0 * K * 2.0 / 48e3 * (double)((tail_tiles * ts + c->n_cus - 1) / c->n_cus) / (double)ts +
+                                               (double)tail_pad * (double)n_pad_total * 8.0 / 5e6 * (double)ts + 8.0;
+                        const double cost = (double)((m_tiles_main * tiles_n_big + c->n_cus - 1) / c->n_cus) + tail_us / (kRoundUs * K);
+                        if (cost < (double)(full + 1)) {
+                            m_full = (int)(m_tiles_main * 256);
+                            tail_S = (int)ts;
+                            tail_cost = cost;
+                        }
                     }
                 }
             }

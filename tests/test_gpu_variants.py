@@ -210,3 +210,23 @@ def test_turned_k_walk_of_the_128_row_tile(n_tokens):
     # K of gate|up 2048: 32 K tiles, 112 column tiles; and a K that does not turn the walk, behind it on the same sizes
     run_and_check(wl.config2(shrink=2, n_tokens=n_tokens), path=B.LORA_PATH_FUSED, packed=True)
     run_and_check(wl.qwen_decode(shrink=2, n_tokens=n_tokens), path=B.LORA_PATH_FUSED, packed=True)
+
+
+@pytest.mark.parametrize("n_tokens,cols,launches", [
+    # two full rounds of 256 x 256 tiles and 8 rows (their split-K pass costs less than 256 x 192 tiles in three rounds)
+    (8200, 4096, ["gemm_fused_staged_256x256x64_w8", "gemm_splitk_shrink_256x128x64_w8", "reduce_expand"]),
+    # one full round would be followed by 1104 rows, more than the split-K path takes
+    (5200, 4096, ["gemm_fused_staged_256x192x64_w8"]),
+])
+def test_rows_behind_the_full_rounds(n_tokens, cols, launches):
+    ids = np.full(n_tokens, -1, dtype=np.int32)
+    w = wl.custom("tail", 12, [(4096, cols)], ["p"], 1, 8, wl.BUCKET_RUNS, ids, {0: 8}, resident=[])
+    sess = Session(w)
+    try:
+        sess.bucket()
+        y = sess.forward(0).float()
+        assert B.lora_last_launches(sess.ctx) == launches
+        ref = sess.x[0].float() @ sess.W[0].float().t().contiguous()
+        assert float((y - ref).abs().max() / ref.abs().max()) <= 5e-3
+    finally:
+        sess.close()
