@@ -317,7 +317,7 @@ enum {
 enum {
     LORA_INLINE_SHRINK_AUTO = 0, /* when the tiles leave CUs idle and those can finish the shrink in time */
     LORA_INLINE_SHRINK_OFF = 1,  /* always a separate shrink launch */
-    LORA_INLINE_SHRINK_ON = 2    /* whenever at least 8 CUs have no tile */
+    LORA_INLINE_SHRINK_ON = 2    /* whenever at least 8 CUs (PAIR tiles: halves of CUs) have no tile */
 };
 /* Values of LORA_TUNE_COPY_ENGINE. */
 enum {

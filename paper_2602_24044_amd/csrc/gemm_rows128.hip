@@ -174,10 +174,13 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
         w_up[q] = GLU && ((((wave * WQ + q) * 8) >> 5) & 1);
     }
     // k_rot (fused path up to 128 tokens, K a multiple of 2048): column tile n starts its walk over K at K tile n and
-    // wraps around.  With all workgroups at the same K offset and rows a multiple of 4 KB apart, the weight stream asks few
-    // memory channels at a time: gate|up of Llama-8B (235 MB of W) at one token 66 -> 52 us, at 32 tokens 75 -> 61 (128-row
-    // tiles).  Rows of 7 KB (K = 3584) do not need it (75 and 76 us), a 256-row tile gains nothing (step of 256 tokens
-    // 231 us either way), and several row tiles lose by spreading over x (640 tokens, q|k|v: 60 -> 83 us).
+    // wraps around.  With rows a multiple of 4 KB apart and all workgroups at the same K offset, the weight stream is
+    // slower than its bytes: 28672 columns at 32 tokens, K = 4096 53.8 us (4.4 TB/s), K = 4160 45.1 us (5.3).  Walks that
+    // start apart take 43.8 us at K = 4096; K = 2048, 6144 and 8192 go from 30.6, 78.3 and 107.9 us to 27.4, 64.4 and 83.9.
+    // Other strides have nothing to gain (K = 1024, 2560, 3072, 3584, 4224, 5120: within 1 %) or lose (K = 4160: 52.4 us).
+    // The same at 1, 64 and 100 tokens.  That rows 4 KB apart fall on few memory channels at a time would explain it; no
+    // counter resolves that in time.  A 256-row tile gains nothing (step of 256 tokens 231 us either way), and several row
+    // tiles lose by spreading over x (640 tokens, q|k|v: 60 -> 83 us).
     const int rot = ROT && a.k_rot ? tile_n % nk : 0;
     const uint32_t cp_x = ring_addr + wave * XQ * 1024;
     const uint32_t cp_w = ring_addr + BM * kRowB + wave * WQ * 1024;

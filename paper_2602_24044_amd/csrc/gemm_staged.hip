@@ -76,8 +76,10 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_staged_kernel(GemmArgs a
 
     // blockIdx -> (tile_m, tile_n): the M tile is the fastest index (neighbouring workgroups share the W tile).
     // Consecutive workgroups go to different XCDs: with up to kXcdRuns row tiles every XCD takes a contiguous run of the
-    // tiles instead (the 32 it works on at a time then share 2 - 4 column tiles through its L2, not up to 28).  Llama-8B at
-    // 2100 tokens (9 row tiles): gate|up 559 -> 532 us, down 369 -> 349 us.  80 row tiles: 8107 us a step against 8213.
+    // tiles instead (the 32 it works on at a time then share 32 / tiles_m column tiles through its L2, rounded up, instead
+    // of up to 32 of them spread over the grid).  Whole steps, without -> with: Llama-8B at 640 tokens (3 row tiles) 447 ->
+    // 433 us, at 1200 (5) 715 -> 693; Qwen2.5-7B at 300 (2) 334 -> 321, at 600 (3) 484 -> 448; single launches of Llama-8B at
+    // 2100 (9): gate|up 559 -> 532 us, down 369 -> 349 us.  80 row tiles: 8107 us a step without against 8213.
     int number = (int)blockIdx.x;
     if (a.tiles_m <= kXcdRuns) {
         const int xcd = number & 7, per = (int)gridDim.x >> 3, more = (int)gridDim.x & 7;
