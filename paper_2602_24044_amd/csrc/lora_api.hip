@@ -1188,12 +1188,14 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                     ts = std::min<long>(ts, std::max(1, (K / kBK) / 2));
                     ts = std::min<long>(ts, (long)(scr.part_elems / ((size_t)tail_pad * (size_t)n_pad_total)));
                     if (ts >= 2) {
-                        // in rounds of 256 x 256 tiles (kRoundUs); the tail by the split-K cost model of plan_forward, 8 us for its
-                        // second launch.  Model and measured: 340 rows of Llama-8B q|k|v 0.57 and 0.54, 384 rows of Llama-70B o and
-                        // down 0.37 and 0.43, 0.31 and 0.33.
+                        // In rounds of 256 x 256 tiles (kRoundUs): the split-K cost model of plan_forward, 8 us for the second
+                        // launch, at most half a round.  Model and measured: 340 rows of Llama-8B q|k|v 0.57 and 0.54, 384 rows of
+                        // Llama-70B o and down 0.37 and 0.43, 0.31 and 0.33; 8 rows of Llama-8B down (8200 tokens) 0.12.  The bound
+                        // is for short K, where the model and the 8 us weigh as much as a round: 4096 columns of K = 512 at 4452
+                        // tokens take 41 us with the tail and 31 us in 256 x 192 tiles, and still take the tail.
                         const double tail_us = 384.0 * K * 2.0 / 48e3 * (double)((tail_tiles * ts + c->n_cus - 1) / c->n_cus) / (double)ts +
                                                (double)tail_pad * (double)n_pad_total * 8.0 / 5e6 * (double)ts + 8.0;
-                        const double cost = (double)((m_tiles_main * tiles_n_big + c->n_cus - 1) / c->n_cus) + tail_us / (kRoundUs * K);
+                        const double cost = (double)((m_tiles_main * tiles_n_big + c->n_cus - 1) / c->n_cus) + std::min(0.5, tail_us / (kRoundUs * K));
                         if (cost < (double)(full + 1)) {
                             m_full = (int)(m_tiles_main * 256);
                             tail_S = (int)ts;
