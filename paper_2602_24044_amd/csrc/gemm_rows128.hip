@@ -238,8 +238,8 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     bool early = false;
     const bool poll_on = PRE && front > 0 && nk >= kPollTile;
     const uint32_t poll_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)s_poll;
-    if constexpr (PRE) {
-        if (front > 0 && tid == 0) s_poll[0] = 0u;           // a word that has not landed reads as "not yet"
+    if constexpr (PRE && kPollYoungest) {
+        if (front > 0 && tid == 0) s_poll[0] = 0u;           // a word that has not landed would read as "not yet"
     }
     // Past the wait for the shrink workgroups every tile workgroup takes a ticket; the one with the last ticket
     // sets the two counters back to zero for the next launch (at the end of the kernel: nobody of this launch
