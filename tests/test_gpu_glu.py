@@ -125,3 +125,36 @@ def test_gated_tile_by_rounds(n_tokens, cols, kernel):
     ids = np.repeat(rng.integers(-1, 6, size=n_tokens // 10 + 1), 10)[:n_tokens].astype(np.int32)
     w = wl.custom("glu_rounds", 8, [(64, cols), (64, cols)], ["gate", "up"], 6, 16, wl.BUCKET_SORTED, ids, {i: 8 * (1 + i % 2) for i in range(6)})
     _run(w, kernel)
+
+
+@pytest.mark.parametrize("mode", [B.LORA_INLINE_SHRINK_OFF, B.LORA_INLINE_SHRINK_ON])
+@pytest.mark.parametrize("n_tokens,kernel", [(1, "gemm_glu_64x128x64_w4"), (64, "gemm_glu_64x128x64_w4"), (65, "gemm_glu_128x128x64_w4"),
+                                             (129, "gemm_glu_256x128x64_w8")])
+def test_gated_shrink_inside_and_outside_the_launch(n_tokens, kernel, mode):
+    # an adapter of the largest rank per token over a short K: the tiles arrive first.  Every second launch has NaN for x, so
+    # a tile that does not wait for its own launch's shrink results shows it
+    n_ad = min(n_tokens, 64)
+    ids = (np.arange(n_tokens) % n_ad).astype(np.int32)
+    w = wl.custom("glu_late_shrink", 43 + n_tokens, [(512, 1792), (512, 1792)], ["gate", "up"], n_ad, 64, wl.BUCKET_SORTED, ids,
+                  {i: 64 for i in range(n_ad)})
+    announce(f"glu wait T={n_tokens} mode={mode} {kernel}")
+    sess = Session(w)
+    try:
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_INLINE_SHRINK, mode)
+        sess.load(w.resident)
+        sess.bucket()
+        x_ok, x_nan = sess.x, [torch.full_like(t, float("nan")) for t in sess.x]
+        outs = []
+        for rep in range(20):
+            sess.x = x_nan if rep % 2 == 0 else x_ok
+            y = sess.forward_glu(0, 1)
+            assert B.lora_last_launches(sess.ctx) == (["shrink"] if mode == B.LORA_INLINE_SHRINK_OFF else []) + [kernel]
+            if rep % 2:
+                outs.append(y)
+        torch.cuda.synchronize()
+        h_ref = oracle.gated(w.x[0], w.W[0], w.W[1], w.token_ids, oracle.adapters_of(w, 0), oracle.adapters_of(w, 1))
+        assert rel_err(bf16_tensor_to_bits(outs[0]), h_ref) <= TOL
+        assert all(torch.equal(y, outs[0]) for y in outs)
+        assert B.lora_poll_device_flags(sess.ctx) == (B.LORA_OK, 0)
+    finally:
+        sess.close()
