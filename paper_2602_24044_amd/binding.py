@@ -82,7 +82,8 @@ FUSED_VARIANTS = {"256x256x32_w4": 1, "256x256x32_w4_3stages": 2, "128x128x32_w4
                   "256x256x32_w8": 12, "256x128x64_w4": 13, "256x256x64_w4": 14,
                   "staged_256x256x64_w8": 15, "staged_256x256x64_w4": 16,
                   "32x128x64_w4": 20, "64x128x64_w4": 21, "32x128x64_w4_pair": 22, "64x128x64_w4_pair": 23,
-                  "staged_256x192x64_w8": 30, "staged_128x256x64_w8": 31}
+                  "staged_256x192x64_w8": 30, "staged_128x256x64_w8": 31,
+                  "direct_256x256x64_w4": 33, "direct_256x192x64_w4": 34, "direct_128x256x64_w4": 35}
 SPLIT_VARIANTS = {"256x128x32_w4": 1, "256x64x32_w4": 2, "128x128x32_w4": 3, "128x128x32_w4_8stages": 4,
                   "256x128x64_w8": 6, "128x128x64_w4": 7, "256x128x32_w8": 8, "256x128x64_w4": 9,
                   "32x128x64_w4": 10, "64x128x64_w4": 11}

@@ -136,25 +136,46 @@ int auto_split_cap(int N, int n_cus)
     return std::max(1, std::min(16, s));
 }
 
-// Tile shape of the register-staged fused GEMM: rounds of workgroups over the CUs times the measured time of a round
-// relative to one of 256 x 256 tiles (K = 4096: 116 us; 256 x 192: 92; 128 x 256: 73; 128 x 128, the 32-wide kernel: 45).
+// The kernel for large batches that copies straight to LDS (gemm_direct.hip) addresses x, W and the output with 32-bit byte
+// offsets through buffers, walks at least three K tiles and keeps what its expand needs in the call's scratch for partial tiles.
+constexpr int kDirect = LORA_FUSED_DIRECT_256x256x64_W4, kDirect192 = LORA_FUSED_DIRECT_256x192x64_W4, kDirect128 = LORA_FUSED_DIRECT_128x256x64_W4;
+bool fused_direct(int fv) { return fv >= kDirect && fv <= kDirect128; }
+// Lays the arrays of ExpandTiles out in `at`; returns the bytes they take.
+size_t place_expand_tiles(ExpandTiles& ex, char* at, int n, int32_t T, int32_t max_rank)
+{
+    const size_t blocks = ((size_t)T + 255) / 256;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { char* p = at + o; o = align_up(o + bytes, kAlign); return p; };
+    ex.count = reinterpret_cast<int32_t*>(take(4 * blocks));
+    ex.row = reinterpret_cast<int32_t*>(take(4 * (size_t)T));
+    ex.window = reinterpret_cast<int32_t*>(take(4 * (((size_t)T + 15) / 16)));
+    ex.record = reinterpret_cast<int2*>(take(8 * blocks * 256 * (size_t)(max_rank / 8)));
+    ex.zero = reinterpret_cast<int32_t*>(take(16));
+    ex.v = reinterpret_cast<uint16_t*>(take(2 * (size_t)n * (size_t)T * (size_t)max_rank));
+    return o;
+}
+
+// Tile shape of the fused GEMM for large batches: rounds of workgroups over the CUs times the measured time of a round
+// relative to one of 256 x 256 tiles.  K = 4096, tiles copied straight to LDS: 256 x 256 100 us, 256 x 192 79, 128 x 256 59,
+// 128 x 128 (the 32-wide kernel) 41.5; tiles staged through registers: 116, 92, 73, 45.
 // Large problems take the big tile, and so do near ties; a projection with few big tiles (o and down at a few thousand
-// tokens) fills the chip better with smaller ones.  Llama-8B, 256 x 256 tiles -> this choice: 2100 tokens o 120 -> 94 us,
+// tokens) fills the chip better with smaller ones.  Staged tiles, Llama-8B, 256 x 256 -> this choice: 2100 tokens o 120 -> 94 us,
 // down 351 -> 281; 1300 tokens (before: 256 x 128 tiles of the 32-wide kernel) o 80 -> 73, down 232 -> 216, q|k|v 120 -> 94.
 // tail: cost of 256 x 256 tiles when the rows behind the full rounds go to the split-K path (0: they do not).
-constexpr double kRoundUs = 116.0 / 4096;    // a round of 256 x 256 tiles, per element of K
+constexpr double kRoundUs = 100.0 / 4096, kStagedRoundUs = 116.0 / 4096;    // a round of 256 x 256 tiles, per element of K
 constexpr int kStaged192 = LORA_FUSED_STAGED_256x192x64_W8, kStaged128 = LORA_FUSED_STAGED_128x256x64_W8;
+struct FusedTile { int v, bm, bn; double round; };
 template <typename TilesOf>
-int pick_fused_variant(int n_cus, TilesOf&& tiles_of, double tail)
+int pick_fused_variant(int n_cus, TilesOf&& tiles_of, double tail, bool direct)
 {
-    const struct { int v, bm, bn; double round; } cand[] = {
-        {0, 256, 256, 1.0}, {kStaged192, 256, 192, 0.78}, {kStaged128, 128, 256, 0.63}, {3, 128, 128, 0.385}};
+    static const FusedTile staged[] = {{0, 256, 256, 1.0}, {kStaged192, 256, 192, 0.78}, {kStaged128, 128, 256, 0.63}, {3, 128, 128, 0.385}};
+    static const FusedTile copied[] = {{kDirect, 256, 256, 1.0}, {kDirect192, 256, 192, 0.79}, {kDirect128, 128, 256, 0.59}, {3, 128, 128, 0.415}};
     int v = 0;
     double best = 0.0;
-    for (const auto& cd : cand) {
+    for (const FusedTile& cd : direct ? copied : staged) {
         const long tiles = tiles_of(cd.bm, cd.bn);
         double cost = (double)((tiles + n_cus - 1) / n_cus) * cd.round;
-        if (cd.v == 0 && tail > 0.0) cost = std::min(cost, tail);
+        if (cd.bm == 256 && cd.bn == 256 && tail > 0.0) cost = std::min(cost, tail);
         if (best == 0.0 || cost < best * 0.97) {
             best = cost;
             v = cd.v;
@@ -276,6 +297,7 @@ struct lora_ctx {
     std::vector<int32_t> slot_first_page, page_owner;
     uint64_t tick = 0;
     int n_resident = 0;
+    long ranks_resident = 0;                // their ranks, summed
 
     // stream ordering
     hipEvent_t ev_meta = nullptr, ev_fwd = nullptr;
@@ -818,7 +840,11 @@ lora_status lora_slots_load(lora_ctx* c, int32_t n, lora_adapter_desc* descs, co
     c->page_owner.swap(owner);
     c->tick = tick;
     c->n_resident = 0;
-    for (int k = 0; k < n_slots; ++k) c->n_resident += c->slot_adapter[k] >= 0;
+    c->ranks_resident = 0;
+    for (int k = 0; k < n_slots; ++k) {
+        c->n_resident += c->slot_adapter[k] >= 0;
+        c->ranks_resident += c->slot_rank_h[k];
+    }
     for (int i = 0; i < n; ++i) {
         descs[i].slot = out_slot[i];
         descs[i].copied = out_copied[i];
@@ -1148,6 +1174,19 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         // ---- shrink, then base GEMM with the expand in its epilogue ----
         int fv = c->tune[LORA_TUNE_FUSED_VARIANT];
         const bool auto_variant = fv == 0 && !glu;
+        const bool direct_ok = [&] {
+            ExpandTiles probe;
+            return K >= 3 * kBK && (uint64_t)T * (uint64_t)plan.n_max < (1ull << 31) - 128 && !over_byte_offsets((uint64_t)T, K) &&
+                   !over_byte_offsets((uint64_t)plan.n_max, K) &&
+                   (!sa.on || place_expand_tiles(probe, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank) <= scr.part_elems * 4);
+        }();
+        // The expand of a 256-row block takes a K tile per 64 ranks of its adapters (2.5 us each, in the register-staged kernel's
+        // epilogue 1.8).  Where a batch is spread so thinly over so many adapters that these outnumber 0.4 of the backbone's K
+        // tiles, that kernel is the faster one: Llama-8B gate|up, 512 tokens of 285 adapters of 30 ranks each, 70 tiles behind 64:
+        // 238 us against 278.  Estimated from the adapters that are resident, evenly spread.
+        const double blocks = std::max(1.0, (double)T / 256.0);
+        const double block_ranks = (glu ? 2.0 : 1.0) * (double)c->ranks_resident / std::max(1, c->n_resident) * std::min(256.0, 1.0 + c->n_resident / blocks);
+        const bool direct = direct_ok && (!sa.on || block_ranks <= 0.4 * K);
         // Up to 64 tokens the tile has 32 or 64 rows; with more such tiles than CUs, the variant of which two workgroups
         // share a CU.
         auto small_variant = [&](int one, int pair, long tiles) { return tiles <= c->n_cus ? one : pair; };
@@ -1158,14 +1197,14 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         // half of those.  Whole step, 256 x 128 -> 256 x 256, rounds in brackets: Llama-8B 400 tokens 328 -> 314 us (2, 1), 850
         // tokens 609 -> 568 (4, 2), but 640 tokens 468 -> 497 (3, 2); Qwen2.5-7B 640 tokens 517 -> 487 (4, 2), but 340 tokens
         // 380 -> 410 (3, 2) and 850 tokens 677 -> 689 (5, 3).
-        if (glu) {
+        if (glu && !fused_direct(fv)) {
             auto rounds = [&](long tiles) { return (tiles + c->n_cus - 1) / c->n_cus; };
             const long big = tiles_of(256, 256);
             const bool staged = T > kSplitMaxTokens ||
                                 (T > 256 && big >= c->n_cus * 3 / 4 && 2 * rounds(big) <= rounds(tiles_of(256, 128)));
             fv = T <= 64    ? small_variant(kFused64, kFusedPair64, tiles_of(64, 128))
                  : T <= 128 ? (tiles_of(128, 128) >= c->n_cus / 2 ? kGlu128W8 : 9)
-                            : (staged ? 0 : 8);
+                            : (staged ? (direct ? kDirect : 0) : 8);
         }
         // A last round of 256 x 256 tiles that fills less than half the chip costs as much as a full one.  When
         // the rows behind the full rounds are few enough for the split-K path, the fused launch can stop at the
@@ -1195,7 +1234,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                         // tokens take 41 us with the tail and 31 us in 256 x 192 tiles, and still take the tail.
                         const double tail_us = 384.0 * K * 2.0 / 48e3 * (double)((tail_tiles * ts + c->n_cus - 1) / c->n_cus) / (double)ts +
                                                (double)tail_pad * (double)n_pad_total * 8.0 / 5e6 * (double)ts + 8.0;
-                        const double cost = (double)((m_tiles_main * tiles_n_big + c->n_cus - 1) / c->n_cus) + std::min(0.5, tail_us / (kRoundUs * K));
+                        const double cost = (double)((m_tiles_main * tiles_n_big + c->n_cus - 1) / c->n_cus) + std::min(0.5, tail_us / ((direct ? kRoundUs : kStagedRoundUs) * K));
                         if (cost < (double)(full + 1)) {
                             m_full = (int)(m_tiles_main * 256);
                             tail_S = (int)ts;
@@ -1206,7 +1245,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             }
         }
         if (auto_variant) {
-            fv = pick_fused_variant(c->n_cus, tiles_of, tail_cost);
+            fv = pick_fused_variant(c->n_cus, tiles_of, tail_cost, direct);
             // small batch: bound by the copies, not by the MFMA issue: whole-line tiles, every wave copies
             // (128-row tiles up to 128 tokens)
             if (T <= 64)
@@ -1238,7 +1277,8 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             }
         }
         if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)plan.n_max, K)) && !fused_wide_k(fv, glu)) fv = glu ? 8 : 10;
-        const bool use_tail = auto_variant && fv == 0 && m_full < T;
+        if (fused_direct(fv) && !direct_ok) fv = 0;
+        const bool use_tail = auto_variant && (fv == 0 || fv == kDirect) && m_full < T;
         const int m_split = use_tail ? m_full : T;
         // Small batches leave CUs without a tile (224 tiles of 256 x 128 for a Llama-8B gate|up, 198 of 256 x 192
         // for Qwen2.5-7B).  When those CUs can finish the shrink well inside the time the tiles stream, they do
@@ -1288,7 +1328,18 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             a.k_rot = T <= 128 && K % 2048 == 0 ? 1 : 0;
             // 8 .. 11, 13, 14, 20 .. 23: 64-wide K tiles through the copy instruction; 12: the 32-wide 256 x 256 eight-wave kernel
             const int wide = fv >= kFused32 ? fv - kFused32 + 6 : fv >= 13 ? fv - 9 : fv - 8;
-            const hipError_t le = glu ? (fv == 0 ? launch_gemm_staged_glu(a, s, &name) : launch_gemm_rows128_glu(a, sa, wide, s, &name))
+            a.ex.on = 0;
+            if (fused_direct(fv) && sa.on) {
+                a.ex.on = 1;
+                place_expand_tiles(a.ex, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank);
+            }
+            // The launch log calls the tiles of the automatic choice by one name, whichever of the two kernels serves them.
+            static const char* const kTileNames[2][3] = {
+                {"gemm_fused_staged_256x256x64_w8", "gemm_fused_staged_256x192x64_w8", "gemm_fused_staged_128x256x64_w8"},
+                {"gemm_fused_direct_256x256x64_w4", "gemm_fused_direct_256x192x64_w4", "gemm_fused_direct_128x256x64_w4"}};
+            if (fused_direct(fv)) name = glu ? "gemm_glu_staged_256x256x64_w8" : kTileNames[auto_variant ? 0 : 1][fv - kDirect];
+            const hipError_t le = fused_direct(fv) ? (glu ? launch_gemm_direct_glu(a, c->n_cus, s) : launch_gemm_direct_fused(a, fv - kDirect, c->n_cus, s))
+                                  : glu ? (fv == 0 ? launch_gemm_staged_glu(a, s, &name) : launch_gemm_rows128_glu(a, sa, wide, s, &name))
                                   : fused_wide_k(fv, false)
                                       ? launch_gemm_rows128_fused(a, sa, wide, s, &name)
                                       // 0 (the big tile of the automatic choice), 15, 16: tiles staged through registers

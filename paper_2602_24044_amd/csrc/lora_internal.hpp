@@ -122,9 +122,23 @@ struct ShrinkArgs {
     int32_t on;          // 0: nothing to shrink (no adapter resident)
 };
 
+// What the GEMM kernel for large batches needs to run the expand as further K tiles (gemm_direct.hip), written by a small
+// launch in front of it into scratch of the call.
+struct ExpandTiles {
+    int32_t on;          // 0: no adapter resident, nothing to expand
+    int32_t pad_;
+    int32_t* count;      // [blocks of 256 rows] chunks of eight ranks in the block
+    int32_t* row;        // [T] first chunk of the row's adapter in its block | chunks << 16
+    int32_t* window;     // [T / 16, rounded up] first chunk of the window's rows | end << 16 (0: none)
+    int2* record;        // [blocks][256 max_rank / 8] location of the adapter, its rank | first of the chunk's ranks << 8
+    int32_t* zero;       // [4] zeros
+    uint16_t* v;         // [slices][T][max_rank] bf16: scaled shrink results
+};
+
 struct GemmArgs {
     DeviceView dv;
     GroupArgs g;
+    ExpandTiles ex;
     int32_t K;
     int32_t tiles_m, tiles_n;   // tiles_n counts the tiles of all slices
     int32_t split_k;     // 1 on the fused path
@@ -178,6 +192,9 @@ hipError_t launch_gemm_rows128_glu(const GemmArgs& a, const ShrinkArgs& none, in
                                    const char** name);
 hipError_t launch_gemm_staged_glu(const GemmArgs& a, hipStream_t stream, const char** name);
 hipError_t launch_gemm_staged_fused(const GemmArgs& a, int variant, hipStream_t stream, const char** name);
+// large batches: tiles copied straight to LDS, the expand as further K tiles; tile 0: 256 x 256, 1: 256 x 192, 2: 128 x 256
+hipError_t launch_gemm_direct_fused(const GemmArgs& a, int tile, int n_cus, hipStream_t stream);
+hipError_t launch_gemm_direct_glu(const GemmArgs& a, int n_cus, hipStream_t stream);
 hipError_t launch_reduce_expand(const ReduceArgs& a, int grid, hipStream_t stream);
 
 }  // namespace lora

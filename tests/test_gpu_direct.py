@@ -1,0 +1,127 @@
+"""GPU parity of the prefill tiles that are copied straight to LDS and run the expand as further K tiles: sizes at the edges
+of tiles, several tiles per workgroup, blocks whose adapters take one K tile, many and none, a captured launch, and an
+adapter whose values are not finite."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import TOL, announce, rel_err, run_and_check
+from paper_2602_24044_amd import binding as B
+from paper_2602_24044_amd import workloads as wl
+from paper_2602_24044_amd.runtime import Session, bf16_tensor_to_bits
+
+pytestmark = pytest.mark.gpu
+
+TILES = [B.FUSED_VARIANTS[n] for n in ("direct_256x256x64_w4", "direct_256x192x64_w4", "direct_128x256x64_w4")]
+
+
+def _runs(rng, n_tokens, n_ad, longest):
+    """Whole prompts in token order, some without an adapter."""
+    return np.repeat(rng.integers(-1, n_ad, size=n_tokens), rng.integers(1, longest + 1, size=n_tokens))[:n_tokens].astype(np.int32)
+
+
+@pytest.mark.parametrize("variant", TILES)
+@pytest.mark.parametrize("n_tokens,proj,mode,ranks", [
+    (1, [(192, 8)], wl.BUCKET_SORTED, [64]),                                   # three K tiles, one row, one chunk of columns
+    (129, [(256, 200), (256, 256)], wl.BUCKET_SORTED, [8, 16]),
+    (256, [(192, 264)], wl.BUCKET_RUNS, [8]),
+    (257, [(320, 520), (320, 72), (320, 192)], wl.BUCKET_RUNS, [8, 16, 32, 64]),
+    (1030, [(192, 16392)], wl.BUCKET_RUNS, [16, 64]),                          # more tiles than CUs with every tile shape
+])
+def test_tile_edges(n_tokens, proj, mode, ranks, variant):
+    rng = np.random.default_rng(n_tokens)
+    ids = _runs(rng, n_tokens, 6, 90) if mode == wl.BUCKET_RUNS else rng.integers(-1, 6, size=n_tokens).astype(np.int32)
+    w = wl.custom("direct_edges", n_tokens, proj, [f"p{k}" for k in range(len(proj))], 6, 64, mode, ids, {i: ranks[i % len(ranks)] for i in range(6)})
+    run_and_check(w, path=B.LORA_PATH_FUSED, tuning={B.LORA_TUNE_FUSED_VARIANT: variant})
+
+
+@pytest.mark.parametrize("variant", TILES)
+def test_bias_and_packed_slices(variant):
+    run_and_check(wl.qwen_decode(shrink=8, n_tokens=300), path=B.LORA_PATH_FUSED, packed=True, tuning={B.LORA_TUNE_FUSED_VARIANT: variant})
+
+
+@pytest.mark.parametrize("n_ad", [0, 1, 40, 150])
+def test_adapters_per_block(n_ad):
+    # 300 tokens of so many adapters of rank 64: none, one, 40 and 150 K tiles of the expand behind four of the backbone
+    ids = (np.arange(300) % max(n_ad, 1)).astype(np.int32) if n_ad else np.full(300, -1, dtype=np.int32)
+    w = wl.custom("direct_adapters", n_ad, [(256, 264)], ["p"], max(n_ad, 1), 64, wl.BUCKET_SORTED, ids, {i: 64 for i in range(max(n_ad, 1))})
+    for variant in TILES:
+        run_and_check(w, path=B.LORA_PATH_FUSED, tuning={B.LORA_TUNE_FUSED_VARIANT: variant})
+
+
+def _gated(w, tuning):
+    announce(f"glu direct {w.name} T={w.T} proj={w.proj[0]}")
+    sess = Session(w)
+    try:
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_FUSED_VARIANT, tuning)
+        sess.load(w.resident)
+        sess.bucket()
+        out = sess.forward_glu(0, 1)
+        torch.cuda.synchronize()
+        h_ref = oracle.gated(w.x[0], w.W[0], w.W[1], w.token_ids, oracle.adapters_of(w, 0), oracle.adapters_of(w, 1))
+        assert rel_err(bf16_tensor_to_bits(out), h_ref) <= TOL
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("n_tokens,cols,ranks", [(1, 8, [16]), (255, 136, [8, 64]), (257, 1000, [16]), (1100, 8200, [8, 16, 32])])
+def test_gated_tiles(n_tokens, cols, ranks):
+    rng = np.random.default_rng(cols)
+    w = wl.custom("direct_glu", cols, [(192, cols), (192, cols)], ["gate", "up"], 6, 64, wl.BUCKET_RUNS, _runs(rng, n_tokens, 6, 60),
+                  {i: ranks[i % len(ranks)] for i in range(6)})
+    _gated(w, TILES[0])
+
+
+def test_captured_launch_on_new_token_ids():
+    rng = np.random.default_rng(3)
+    w = wl.custom("direct_graph", 3, [(256, 1032)], ["p"], 6, 32, wl.BUCKET_SORTED, rng.integers(-1, 6, size=1100).astype(np.int32),
+                  {i: 8 << (i % 3) for i in range(6)})
+    sess = Session(w)
+    try:
+        sess.load(w.resident)
+        sess.step()
+        torch.cuda.synchronize()
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            sess.step()
+        side.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            sess.step()
+        for rep in range(3):
+            ids = rng.integers(-1, 6 if rep != 1 else 1, size=w.T).astype(np.int32)
+            sess.ids.copy_(torch.from_numpy(ids).to(sess.device))
+            sess.out[0].zero_()
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            y_ref = oracle.project(w.x[0], w.W[0], ids, oracle.adapters_of(w, 0))
+            assert rel_err(bf16_tensor_to_bits(sess.out[0]), y_ref) <= TOL, rep
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("variant", TILES)
+def test_values_that_are_not_finite_stay_with_their_adapter(variant):
+    # tokens of adapter 1 sit between those of 0 and 2; its B holds an infinity, which must reach its own 16-row windows only
+    ids = np.repeat(np.arange(3, dtype=np.int32), 48)
+    w = wl.custom("direct_inf", 1, [(192, 264)], ["p"], 3, 16, wl.BUCKET_RUNS, ids, {0: 16, 1: 16, 2: 8})
+    outs = []
+    for poison in (False, True):
+        if poison:
+            w.adapters[1].B[0][:, 3] = 0x7f80                  # + infinity in bf16
+        sess = Session(w, path=B.LORA_PATH_FUSED)
+        try:
+            B.lora_set_tuning(sess.ctx, B.LORA_TUNE_FUSED_VARIANT, variant)
+            sess.load(w.resident)
+            sess.bucket()
+            outs.append(sess.forward(0).clone())
+            torch.cuda.synchronize()
+        finally:
+            sess.close()
+    clean, poisoned = outs
+    assert bool(torch.isfinite(clean).all())
+    assert not bool(torch.isfinite(poisoned[48:96]).any())
+    assert torch.equal(clean[:48], poisoned[:48]) and torch.equal(clean[96:], poisoned[96:])
