@@ -58,7 +58,8 @@ __device__ inline void copy16_to_lds(const void* base, uint32_t byte_off, uint32
     // it) and needs none: the compiler keeps no value in m0 between statements, it writes m0 itself directly in
     // front of each instruction of its own that reads it.  Putting the old value back after the copy was tried
     // and stalls every copy (the write to m0 waits until the copy instruction has read it): + 0.2 us per K tile.
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory");
+    // The hardware wants one wait state between a scalar write of m0 and a copy instruction that reads it.
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "memory");
 }
 
 template <int N>

@@ -27,7 +27,10 @@ namespace {
 constexpr int kTK64 = 64;    // K extent of one LDS tile (bf16 elements): 128-byte rows
 constexpr int kRowB = 128;
 
-__device__ inline void copy16_to_lds(const void* gptr, uint32_t lds_addr)
+// Takes the lane's address `step` bytes on and copies 16 bytes from there.  (The hardware wants one wait state between the
+// scalar write of m0 and the copy instruction that reads it: the step of the address fills it.  An s_nop in its place costs a
+// step of 32 tokens 0.7 %.)
+__device__ inline void copy16_to_lds(uint64_t& gptr, uint64_t step, uint32_t lds_addr)
 {
     // issued from inline assembly: the only ordering against later LDS reads is the explicit vmcnt wait +
     // barrier of the main loop
@@ -35,14 +38,14 @@ __device__ inline void copy16_to_lds(const void* gptr, uint32_t lds_addr)
     // it) and needs none: the compiler keeps no value in m0 between statements, it writes m0 itself directly in
     // front of each instruction of its own that reads it.  Putting the old value back after the copy was tried
     // and stalls every copy (the write to m0 waits until the copy instruction has read it): + 0.2 us per K tile.
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_addr) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\tv_lshl_add_u64 %0, %0, 0, %2\n\tglobal_load_lds_dwordx4 %0, off" : "+v"(gptr) : "s"(lds_addr), "s"(step) : "memory");
 }
 
 // One dword per lane, global -> LDS (lane l lands at lds_addr + 4 l), coherent at device scope: the poll of a
 // counter that other workgroups of the launch advance.
 __device__ inline void poll4_to_lds(const void* gptr, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off sc1" ::"v"(gptr), "s"(lds_addr) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off sc1" ::"v"(gptr), "s"(lds_addr) : "memory");
 }
 
 template <int N>
@@ -154,24 +157,26 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     // Copy assignment: instruction q of wave w fills stage rows 8 (w XQ + q) .. + 7 of the x part (same for
     // the W part with WQ); lane l owns row l / 8 of those and chunk position l % 8.  Rows past T or N are
     // clamped to the last valid row: they are computed, never stored.
-    uint32_t xoff[XQ], woff[WQ];                            // element offsets of this lane's 16 bytes in tile 0
+    // k_rot: see below
+    const int rot = ROT && a.k_rot ? tile_n % nk : 0;
+    uint64_t xat[XQ], wat[WQ];                              // where this lane's 16 bytes of the last tile copied lie
+    const size_t first = (size_t)(kt_begin + rot) * kTK64 * 2 - kTK64 * 2;
 #pragma unroll
     for (int q = 0; q < XQ; ++q) {
         const int r = (wave * XQ + q) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
         int m = m0 + r;
         if (m > T - 1) m = T - 1;
-        xoff[q] = (uint32_t)a.dv.perm[m] * (uint32_t)K + (uint32_t)(c * 8 + kt_begin * kTK64);
+        xat[q] = (uint64_t)(xg + ((uint32_t)a.dv.perm[m] * (uint32_t)K + (uint32_t)(c * 8))) + first;
     }
-    bool w_up[WQ];                                           // GLU: this copy instruction's rows come from `up` (uniform over the wave)
 #pragma unroll
     for (int q = 0; q < WQ; ++q) {
         const int r = (wave * WQ + q) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
         int n = GLU ? n0 + (r >> 6) * 32 + (r & 31) : n0 + r;
         if (n > N - 1) n = N - 1;
-        woff[q] = (uint32_t)n * (uint32_t)K + (uint32_t)(c * 8 + kt_begin * kTK64);
-        w_up[q] = GLU && ((((wave * WQ + q) * 8) >> 5) & 1);
+        const bool w_up = GLU && ((((wave * WQ + q) * 8) >> 5) & 1);      // GLU: this instruction's rows come from `up` (uniform over the wave)
+        wat[q] = (uint64_t)((w_up ? Wup : Wg) + ((uint32_t)n * (uint32_t)K + (uint32_t)(c * 8))) + first;
     }
     // k_rot (fused path up to 128 tokens, K a multiple of 2048): column tile n starts its walk over K at K tile n and
     // wraps around.  With rows a multiple of 4 KB apart and all workgroups at the same K offset, the weight stream is
@@ -181,24 +186,22 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_rows128_kernel(GemmArgs 
     // The same at 1, 64 and 100 tokens.  That rows 4 KB apart fall on few memory channels at a time would explain it; no
     // counter resolves that in time.  A 256-row tile gains nothing (step of 256 tokens 231 us either way), and several row
     // tiles lose by spreading over x (640 tokens, q|k|v: 60 -> 83 us).
-    const int rot = ROT && a.k_rot ? tile_n % nk : 0;
     const uint32_t cp_x = ring_addr + wave * XQ * 1024;
     const uint32_t cp_w = ring_addr + BM * kRowB + wave * WQ * 1024;
-    // copy instructions [q_begin, q_end) of tile t of this workgroup's K range; the W rows (from HBM) go first
+    // copy instructions [q_begin, q_end) of tile t of this workgroup's K range; the W rows (from HBM) go first.  Tiles are
+    // copied in order, every instruction of a tile once.
     auto copy_part = [&](int t, int stage, int q_begin, int q_end) {
-        int tk = t;
-        if (ROT) {                                           // see above: where this workgroup's walk over K starts
-            tk += rot;
-            if (tk >= nk) tk -= nk;
-        }
-        const uint32_t k0 = (uint32_t)tk * kTK64, so = (uint32_t)stage * STAGE_B;
+        const uint32_t so = (uint32_t)stage * STAGE_B;
+        // a walk that started elsewhere (see above) wraps around in front of tile nk - rot
+        const uint64_t step = ROT ? (uint64_t)(int64_t)__builtin_amdgcn_readfirstlane(t + rot == nk && rot > 0 ? (1 - nk) * (kTK64 * 2) : kTK64 * 2)
+                                  : (uint64_t)(kTK64 * 2);
 #pragma unroll
         for (int q = 0; q < QPT; ++q) {
             if (q < q_begin || q >= q_end) continue;
             if (q < WQ)
-                copy16_to_lds((w_up[q] ? Wup : Wg) + (woff[q] + k0), __builtin_amdgcn_readfirstlane(cp_w + so + q * 1024));
+                copy16_to_lds(wat[q], step, __builtin_amdgcn_readfirstlane(cp_w + so + q * 1024));
             else
-                copy16_to_lds(xg + (xoff[q - WQ] + k0), __builtin_amdgcn_readfirstlane(cp_x + so + (q - WQ) * 1024));
+                copy16_to_lds(xat[q - WQ], step, __builtin_amdgcn_readfirstlane(cp_x + so + (q - WQ) * 1024));
         }
     };
     auto copy_tile = [&](int t, int stage) { copy_part(t, stage, 0, QPT); };
