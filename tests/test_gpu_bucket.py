@@ -117,3 +117,30 @@ def test_sorted_map_whose_last_chunk_is_placed_wave_after_wave(T, n_slots):
             assert check_segments(sess, w) == 0
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("mode", [wl.BUCKET_SORTED, wl.BUCKET_RUNS])
+@pytest.mark.parametrize("T,n_slots", [(1, 4095), (2, 1), (31, 2), (32, 2), (33, 40), (64, 4095), (65, 1), (66, 300), (127, 2), (128, 129), (192, 7),
+                                       (193, 1000), (249, 4095), (255, 64), (256, 1), (257, 64)])
+def test_map_of_a_small_step_with_adapters_that_are_not_resident(mode, T, n_slots):
+    # one token per lane of one wave (up to 64 tokens) or of four (up to 256); whole numbers, so exact
+    w = _bucket_only_workload(T, n_slots, 900 + T, mode)
+    announce(f"bucket small step T={T} n_slots={n_slots} mode={mode}")
+    sess = Session(w, upload_inputs=False)
+    try:
+        rng = np.random.default_rng(T)
+        order = rng.permutation(n_slots)
+        sess.load(list(range(n_slots)), slots=[int(s) for s in order])
+        same = np.full(T, int(w.token_ids.max()), dtype=np.int32)             # one segment
+        turns = (np.arange(T) % min(n_slots, 2)).astype(np.int32)             # a segment per token in RUNS
+        stray = w.token_ids.copy()
+        stray[rng.random(T) < 0.3] = n_slots + 3                              # known, not resident
+        stray[-1] = n_slots + 4
+        for ids, flag in ((w.token_ids, 0), (same, 0), (turns, 0), (stray, oracle.FLAG_NOT_RESIDENT), (rng.permutation(w.token_ids), 0)):
+            w.token_ids = ids
+            sess.bucket(torch.from_numpy(ids).to(sess.device))
+            assert check_segments(sess, w) == flag
+            torch.cuda.synchronize()
+            B.lora_poll_device_flags(sess.ctx)
+    finally:
+        sess.close()
