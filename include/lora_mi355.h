@@ -341,7 +341,8 @@ enum {
     LORA_FUSED_256x128x64_W4 = 13,        /* four wavefronts with 128 x 64 wave tiles: fewer LDS reads per MFMA */
     LORA_FUSED_256x256x64_W4 = 14,
     LORA_FUSED_STAGED_256x256x64_W8 = 15, /* tiles staged through registers (ordinary loads, LDS writes), two LDS stages:
-                                             what LORA_FUSED_AUTO takes above 1024 tokens when the grid fills the chip */
+                                             what LORA_FUSED_AUTO takes for large batches that the DIRECT tiles below do not
+                                             serve (K under 192, 4 GiB operands, scratch limits, very many adapters) */
     LORA_FUSED_STAGED_256x256x64_W4 = 16,
     LORA_FUSED_32x128x64_W4 = 20,         /* what LORA_FUSED_AUTO takes up to 32 and up to 64 tokens; PAIR: two workgroups */
     LORA_FUSED_64x128x64_W4 = 21,         /* per CU, where there are more tiles than CUs */

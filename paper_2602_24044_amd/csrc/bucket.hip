@@ -5,7 +5,7 @@
 // by the slot their adapter occupies so that each adapter's A and B are streamed once per step.
 // SORTED: stable counting sort of token indices by slot; RUNS: token order kept, runs of equal
 // slot.  One 1024-thread workgroup: LDS histogram, LDS prefix scan, wavefront ballots for the
-// stable rank of a token among equal keys.  RUNS above 4096 tokens: one workgroup per 1024 tokens, two launches.
+// stable rank of a token among equal keys.  Up to 256 tokens: one token per lane, places by counting.  RUNS above 4096 tokens: one workgroup per 1024 tokens, two launches.
 #include "lora_internal.hpp"
 
 namespace lora {

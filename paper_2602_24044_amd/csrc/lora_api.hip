@@ -1192,9 +1192,10 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         auto small_variant = [&](int one, int pair, long tiles) { return tiles <= c->n_cus ? one : pair; };
         // gate and up with their product: the 64-wide-K kernel up to 1024 tokens (64-row tiles up to 64, 128-row tiles up
         // to 128, with eight waves where the tiles fill at least half the chip: Llama-8B, 99 tokens, 69 us with four, 66 with
-        // eight), the register-staged 256 x 256 tile above.  It also serves 257 to 1024 tokens where its tiles fill three
-        // quarters of the chip and take half the rounds of the 256 x 128 ones, since a round of it costs more than one and a
-        // half of those.  Whole step, 256 x 128 -> 256 x 256, rounds in brackets: Llama-8B 400 tokens 328 -> 314 us (2, 1), 850
+        // eight), the 256 x 256 tile of the large batches above (copied straight to LDS where that may be, staged through
+        // registers otherwise).  It also serves 257 to 1024 tokens where its tiles fill three quarters of the chip and take half
+        // the rounds of the 256 x 128 ones, since a round of it costs more than one and a half of those.  Whole step,
+        // 256 x 128 -> staged 256 x 256, rounds in brackets: Llama-8B 400 tokens 328 -> 314 us (2, 1), 850
         // tokens 609 -> 568 (4, 2), but 640 tokens 468 -> 497 (3, 2); Qwen2.5-7B 640 tokens 517 -> 487 (4, 2), but 340 tokens
         // 380 -> 410 (3, 2) and 850 tokens 677 -> 689 (5, 3).
         if (glu && !fused_direct(fv)) {
@@ -1264,11 +1265,11 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                         fv = cd.v;
                     }
                 }
-                // From 257 tokens on a launch that wants the wide tiles is bound by the matrix cores: the staged tiles,
-                // although their shrink is a launch of its own (Llama-8B gate|up: 400 tokens 158 -> 141 + 9 us, 640 tokens
+                // From 257 tokens on a launch that wants the wide tiles is bound by the matrix cores: the tiles of the large
+                // batches (staged or copied straight to LDS, `direct`), although their shrink is a launch of its own (staged, Llama-8B gate|up: 400 tokens 158 -> 141 + 9 us, 640 tokens
                 // 245 -> 196, 777 tokens 278 -> 248, 1024 tokens 294 -> 259).  The narrower ones stay: q|k|v and o at 640 -
                 // 1024 tokens 60 and 56 us against 71 and 64.  LORA_INLINE_SHRINK_ON asks for the shrink inside the launch
-                // wherever tiles leave CUs for it: the staged tiles cannot, so such a call keeps the copied ones.
+                // wherever tiles leave CUs for it: those tiles cannot, so such a call keeps the copied ones.
                 int bm, bn;
                 fused_tile(fv, bm, bn);
                 const bool inside = c->tune[LORA_TUNE_INLINE_SHRINK] == LORA_INLINE_SHRINK_ON && !c->inline_shrink_off &&
