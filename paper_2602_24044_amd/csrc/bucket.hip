@@ -5,7 +5,8 @@
 // by the slot their adapter occupies so that each adapter's A and B are streamed once per step.
 // SORTED: stable counting sort of token indices by slot; RUNS: token order kept, runs of equal
 // slot.  One 1024-thread workgroup: LDS histogram, LDS prefix scan, wavefront ballots for the
-// stable rank of a token among equal keys.  Up to 256 tokens: one token per lane, places by counting.  RUNS above 4096 tokens: one workgroup per 1024 tokens, two launches.
+// stable rank of a token among equal keys.  Up to 256 tokens, RUNS up to 1024: one token per lane,
+// places by counting.  RUNS above 4096 tokens: one workgroup per 1024 tokens, two launches.
 #include "lora_internal.hpp"
 
 namespace lora {
@@ -299,7 +300,8 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
 // heads of segments and pieces are numbered from ballots; and the slot tables are read for the tokens' own slots only, in
 // the shadow of the counting.  Under the profiler, large kernel -> this one: 16 tokens
 // 6.3 -> 3.1 us, 1 and 32 tokens of Llama-8B 7.1 -> 4.6, 99 tokens 7.3 -> 4.7, 256 tokens 10.2 -> 6.7.  Above 256 tokens the
-// counting (T compares per token) costs what it saves.
+// counting (T compares per token) costs what it saves (512 tokens with eight waves 9.4 -> 9.1); RUNS counts nothing, and
+// sixteen waves serve it up to 1024 tokens (777 tokens 7.2 -> 5.0).
 constexpr int kSmallWaves = 4;
 
 template <int W>
@@ -561,6 +563,10 @@ hipError_t launch_bucket(const BucketArgs& a, hipStream_t stream)
     }
     if (a.T <= kSmallWaves * kWave) {
         hipLaunchKernelGGL(bucket_small_kernel<kSmallWaves>, dim3(1), dim3(kSmallWaves * kWave), 0, stream, a);
+        return hipGetLastError();
+    }
+    if (a.mode != 0 && a.T <= kNW * kWave) {
+        hipLaunchKernelGGL(bucket_small_kernel<kNW>, dim3(1), dim3(kNW * kWave), 0, stream, a);
         return hipGetLastError();
     }
     if (a.mode != 0 && a.T > kFastT) {

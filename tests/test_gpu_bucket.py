@@ -121,9 +121,10 @@ def test_sorted_map_whose_last_chunk_is_placed_wave_after_wave(T, n_slots):
 
 @pytest.mark.parametrize("mode", [wl.BUCKET_SORTED, wl.BUCKET_RUNS])
 @pytest.mark.parametrize("T,n_slots", [(1, 4095), (2, 1), (31, 2), (32, 2), (33, 40), (64, 4095), (65, 1), (66, 300), (127, 2), (128, 129), (192, 7),
-                                       (193, 1000), (249, 4095), (255, 64), (256, 1), (257, 64)])
+                                       (193, 1000), (249, 4095), (255, 64), (256, 1), (257, 64), (961, 300), (1024, 4)])
 def test_map_of_a_small_step_with_adapters_that_are_not_resident(mode, T, n_slots):
-    # one token per lane of one wave (up to 64 tokens) or of four (up to 256); whole numbers, so exact
+    # one token per lane of one wave (up to 64 tokens), of four (up to 256), RUNS also of sixteen (up to 1024); whole
+    # numbers, so exact
     w = _bucket_only_workload(T, n_slots, 900 + T, mode)
     announce(f"bucket small step T={T} n_slots={n_slots} mode={mode}")
     sess = Session(w, upload_inputs=False)
