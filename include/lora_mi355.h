@@ -351,7 +351,7 @@ enum {
     LORA_FUSED_STAGED_256x192x64_W8 = 30, /* smaller staged tiles, for grids that would leave the last round of the */
     LORA_FUSED_STAGED_128x256x64_W8 = 31, /* 256 x 256 ones mostly empty */
     /* 64-wide K tiles through the copy instruction, the expand as further K tiles, several output tiles per workgroup: what
-       LORA_FUSED_AUTO runs in place of the three staged shapes above (under their names in the launch log) unless K is below
+       LORA_FUSED_AUTO runs in place of the three staged shapes above unless K is below
        192, the output reaches 4 GiB, the scratch is too small or the batch has very many adapters */
     LORA_FUSED_DIRECT_256x256x64_W4 = 33,
     LORA_FUSED_DIRECT_256x192x64_W4 = 34,

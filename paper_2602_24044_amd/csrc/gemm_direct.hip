@@ -680,16 +680,18 @@ hipError_t launch_direct(GemmArgs a, int n_cus, hipStream_t stream)
             a.tiles_n += (a.g.s[k].N + BN - 1) / BN;
         }
     }
-    if (a.ex.on) {
-        hipLaunchKernelGGL(expand_tiles_kernel, dim3((a.dv.T + kDBlock - 1) / kDBlock, a.g.n, kDShares + 1), dim3(kDBlock), 0, stream, a);
-        if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    }
     const int tiles = a.tiles_m * a.tiles_n, grid = tiles < n_cus ? tiles : n_cus;
     hipLaunchKernelGGL((gemm_direct_kernel<BM, BN, GLU, BIAS>), dim3(grid), dim3(kDWaves * kWave), 0, stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
+
+hipError_t launch_expand_tiles(const GemmArgs& a, hipStream_t stream)
+{
+    hipLaunchKernelGGL(expand_tiles_kernel, dim3((a.dv.T + kDBlock - 1) / kDBlock, a.g.n, kDShares + 1), dim3(kDBlock), 0, stream, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_gemm_direct_glu(const GemmArgs& a, int n_cus, hipStream_t stream)
 {

@@ -1312,12 +1312,19 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             LaunchScope ls(c, s, "shrink");
             if (HIP_FAIL(launch_shrink(sa, grid, s))) return LORA_ERR_HIP;
         }
+        GemmArgs a = ga;
+        a.m_end = m_split;
+        a.shrink_front = front;
+        a.ex.on = 0;
+        if (fused_direct(fv) && sa.on) {
+            a.ex.on = 1;
+            place_expand_tiles(a.ex, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank);
+            LaunchScope ls(c, s, "expand_tiles");
+            if (HIP_FAIL(launch_expand_tiles(a, s))) return LORA_ERR_HIP;
+        }
         {
             LaunchScope ls(c, s, "gemm_fused");
             const char* name = nullptr;
-            GemmArgs a = ga;
-            a.m_end = m_split;
-            a.shrink_front = front;
             // LORA_TUNE_SHRINK_WAIT_TEST: the tile workgroups expect one report more than will come and give up
             // after that many polls (host-forced exercise of the expired wait; every kernel still ends normally)
             const int wait_test = c->tune[LORA_TUNE_SHRINK_WAIT_TEST];
@@ -1329,16 +1336,8 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             a.k_rot = T <= 128 && K % 2048 == 0 ? 1 : 0;
             // 8 .. 11, 13, 14, 20 .. 23: 64-wide K tiles through the copy instruction; 12: the 32-wide 256 x 256 eight-wave kernel
             const int wide = fv >= kFused32 ? fv - kFused32 + 6 : fv >= 13 ? fv - 9 : fv - 8;
-            a.ex.on = 0;
-            if (fused_direct(fv) && sa.on) {
-                a.ex.on = 1;
-                place_expand_tiles(a.ex, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank);
-            }
-            // The launch log calls the tiles of the automatic choice by one name, whichever of the two kernels serves them.
-            static const char* const kTileNames[2][3] = {
-                {"gemm_fused_staged_256x256x64_w8", "gemm_fused_staged_256x192x64_w8", "gemm_fused_staged_128x256x64_w8"},
-                {"gemm_fused_direct_256x256x64_w4", "gemm_fused_direct_256x192x64_w4", "gemm_fused_direct_128x256x64_w4"}};
-            if (fused_direct(fv)) name = glu ? "gemm_glu_staged_256x256x64_w8" : kTileNames[auto_variant ? 0 : 1][fv - kDirect];
+            static const char* const kDirectNames[] = {"gemm_fused_direct_256x256x64_w4", "gemm_fused_direct_256x192x64_w4", "gemm_fused_direct_128x256x64_w4"};
+            if (fused_direct(fv)) name = glu ? "gemm_glu_direct_256x256x64_w4" : kDirectNames[fv - kDirect];
             const hipError_t le = fused_direct(fv) ? (glu ? launch_gemm_direct_glu(a, c->n_cus, s) : launch_gemm_direct_fused(a, fv - kDirect, c->n_cus, s))
                                   : glu ? (fv == 0 ? launch_gemm_staged_glu(a, s, &name) : launch_gemm_rows128_glu(a, sa, wide, s, &name))
                                   : fused_wide_k(fv, false)

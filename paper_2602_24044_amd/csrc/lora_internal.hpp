@@ -192,7 +192,9 @@ hipError_t launch_gemm_rows128_glu(const GemmArgs& a, const ShrinkArgs& none, in
                                    const char** name);
 hipError_t launch_gemm_staged_glu(const GemmArgs& a, hipStream_t stream, const char** name);
 hipError_t launch_gemm_staged_fused(const GemmArgs& a, int variant, hipStream_t stream, const char** name);
-// large batches: tiles copied straight to LDS, the expand as further K tiles; tile 0: 256 x 256, 1: 256 x 192, 2: 128 x 256
+// large batches: tiles copied straight to LDS, the expand as further K tiles (what those need is written by
+// launch_expand_tiles, in front, when a.ex.on); tile 0: 256 x 256, 1: 256 x 192, 2: 128 x 256
+hipError_t launch_expand_tiles(const GemmArgs& a, hipStream_t stream);
 hipError_t launch_gemm_direct_fused(const GemmArgs& a, int tile, int n_cus, hipStream_t stream);
 hipError_t launch_gemm_direct_glu(const GemmArgs& a, int n_cus, hipStream_t stream);
 hipError_t launch_reduce_expand(const ReduceArgs& a, int grid, hipStream_t stream);

@@ -13,7 +13,33 @@ from paper_2602_24044_amd.runtime import Session, bf16_tensor_to_bits
 
 pytestmark = pytest.mark.gpu
 
-TILES = [B.FUSED_VARIANTS[n] for n in ("direct_256x256x64_w4", "direct_256x192x64_w4", "direct_128x256x64_w4")]
+NAMES = ["direct_256x256x64_w4", "direct_256x192x64_w4", "direct_128x256x64_w4"]
+TILES = [B.FUSED_VARIANTS[n] for n in NAMES]
+
+
+def _expected(variant, on=True):
+    return (["shrink", "expand_tiles"] if on else []) + ["gemm_fused_" + NAMES[TILES.index(variant)]]
+
+
+def _launches(w, tuning=None, path=B.LORA_PATH_AUTO, gated=False):
+    """Names of the launches of projection 0 (of the gated call of 0 and 1)."""
+    sess = Session(w, path=path)
+    try:
+        for key, value in (tuning or {}).items():
+            B.lora_set_tuning(sess.ctx, key, value)
+        sess.load(w.resident)
+        sess.bucket()
+        sess.forward_glu(0, 1) if gated else sess.forward(0)
+        return B.lora_last_launches(sess.ctx)
+    finally:
+        sess.close()
+
+
+def _check(w, variant, **kw):
+    """The tile that was asked for runs, and its results agree with the oracle."""
+    tuning = {B.LORA_TUNE_FUSED_VARIANT: variant}
+    assert _launches(w, tuning, B.LORA_PATH_FUSED) == _expected(variant, len(w.resident) > 0)
+    run_and_check(w, path=B.LORA_PATH_FUSED, tuning=tuning, **kw)
 
 
 def _runs(rng, n_tokens, n_ad, longest):
@@ -33,12 +59,12 @@ def test_tile_edges(n_tokens, proj, mode, ranks, variant):
     rng = np.random.default_rng(n_tokens)
     ids = _runs(rng, n_tokens, 6, 90) if mode == wl.BUCKET_RUNS else rng.integers(-1, 6, size=n_tokens).astype(np.int32)
     w = wl.custom("direct_edges", n_tokens, proj, [f"p{k}" for k in range(len(proj))], 6, 64, mode, ids, {i: ranks[i % len(ranks)] for i in range(6)})
-    run_and_check(w, path=B.LORA_PATH_FUSED, tuning={B.LORA_TUNE_FUSED_VARIANT: variant})
+    _check(w, variant)
 
 
 @pytest.mark.parametrize("variant", TILES)
 def test_bias_and_packed_slices(variant):
-    run_and_check(wl.qwen_decode(shrink=8, n_tokens=300), path=B.LORA_PATH_FUSED, packed=True, tuning={B.LORA_TUNE_FUSED_VARIANT: variant})
+    _check(wl.qwen_decode(shrink=8, n_tokens=300), variant, packed=True)
 
 
 @pytest.mark.parametrize("n_ad", [0, 1, 40, 150])
@@ -47,7 +73,7 @@ def test_adapters_per_block(n_ad):
     ids = (np.arange(300) % max(n_ad, 1)).astype(np.int32) if n_ad else np.full(300, -1, dtype=np.int32)
     w = wl.custom("direct_adapters", n_ad, [(256, 264)], ["p"], max(n_ad, 1), 64, wl.BUCKET_SORTED, ids, {i: 64 for i in range(max(n_ad, 1))})
     for variant in TILES:
-        run_and_check(w, path=B.LORA_PATH_FUSED, tuning={B.LORA_TUNE_FUSED_VARIANT: variant})
+        _check(w, variant)
 
 
 def _gated(w, tuning):
@@ -59,6 +85,7 @@ def _gated(w, tuning):
         sess.bucket()
         out = sess.forward_glu(0, 1)
         torch.cuda.synchronize()
+        assert B.lora_last_launches(sess.ctx) == ["shrink", "expand_tiles", "gemm_glu_direct_256x256x64_w4"]
         h_ref = oracle.gated(w.x[0], w.W[0], w.W[1], w.token_ids, oracle.adapters_of(w, 0), oracle.adapters_of(w, 1))
         assert rel_err(bf16_tensor_to_bits(out), h_ref) <= TOL
     finally:
@@ -71,6 +98,22 @@ def test_gated_tiles(n_tokens, cols, ranks):
     w = wl.custom("direct_glu", cols, [(192, cols), (192, cols)], ["gate", "up"], 6, 64, wl.BUCKET_RUNS, _runs(rng, n_tokens, 6, 60),
                   {i: ranks[i % len(ranks)] for i in range(6)})
     _gated(w, TILES[0])
+
+
+@pytest.mark.parametrize("n_tokens,cols,gated,kernel", [
+    (1300, 4096, False, "gemm_fused_direct_128x256x64_w4"),
+    (2100, 4104, False, "gemm_fused_direct_256x192x64_w4"),
+    (2049, 28680, False, "gemm_fused_direct_256x256x64_w4"),
+    (257, 28672, False, "gemm_fused_direct_256x256x64_w4"),
+    (777, 14336, True, "gemm_glu_direct_256x256x64_w4"),
+    (1025, 18944, True, "gemm_glu_direct_256x256x64_w4"),
+])
+def test_automatic_choice(n_tokens, cols, gated, kernel):
+    # what runs for large batches of few adapters, and what the launch log calls it
+    rng = np.random.default_rng(n_tokens)
+    proj = [(192, cols)] * (2 if gated else 1)
+    w = wl.custom("direct_auto", 4, proj, ["gate", "up"][:len(proj)], 2, 8, wl.BUCKET_RUNS, _runs(rng, n_tokens, 2, 90), {0: 8, 1: 8})
+    assert _launches(w, gated=gated) == ["shrink", "expand_tiles", kernel]
 
 
 def test_captured_launch_on_new_token_ids():

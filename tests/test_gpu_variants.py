@@ -214,9 +214,9 @@ def test_turned_k_walk_of_the_128_row_tile(n_tokens):
 
 @pytest.mark.parametrize("n_tokens,cols,launches", [
     # two full rounds of 256 x 256 tiles and 8 rows (their split-K pass costs less than 256 x 192 tiles in three rounds)
-    (8200, 4096, ["gemm_fused_staged_256x256x64_w8", "gemm_splitk_shrink_256x128x64_w8", "reduce_expand"]),
+    (8200, 4096, ["gemm_fused_direct_256x256x64_w4", "gemm_splitk_shrink_256x128x64_w8", "reduce_expand"]),
     # one full round would be followed by 1104 rows, more than the split-K path takes
-    (5200, 4096, ["gemm_fused_staged_256x192x64_w8"]),
+    (5200, 4096, ["gemm_fused_direct_256x192x64_w4"]),
 ])
 def test_rows_behind_the_full_rounds(n_tokens, cols, launches):
     ids = np.full(n_tokens, -1, dtype=np.int32)
