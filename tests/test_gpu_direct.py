@@ -67,9 +67,18 @@ def test_bias_and_packed_slices(variant):
     _check(wl.qwen_decode(shrink=8, n_tokens=300), variant, packed=True)
 
 
+@pytest.mark.parametrize("variant", TILES)
+def test_no_adapter_resident(variant):
+    ids = np.full(300, -1, dtype=np.int32)
+    w = wl.custom("direct_base", 2, [(256, 264), (256, 72)], ["p", "r"], 1, 8, wl.BUCKET_SORTED, ids, {0: 8}, resident=[])
+    _check(w, variant)
+    _check(w, variant, packed=True)
+
+
 @pytest.mark.parametrize("n_ad", [0, 1, 40, 150])
 def test_adapters_per_block(n_ad):
-    # 300 tokens of so many adapters of rank 64: none, one, 40 and 150 K tiles of the expand behind four of the backbone
+    # 300 tokens of so many adapters of rank 64 behind four K tiles of the backbone.  The sorted rows' two blocks hold one adapter
+    # each (n_ad = 1), 34 and 7 (40) or 128 and 22 (150), and as many K tiles; n_ad = 0: no row has one, but one is resident
     ids = (np.arange(300) % max(n_ad, 1)).astype(np.int32) if n_ad else np.full(300, -1, dtype=np.int32)
     w = wl.custom("direct_adapters", n_ad, [(256, 264)], ["p"], max(n_ad, 1), 64, wl.BUCKET_SORTED, ids, {i: 64 for i in range(max(n_ad, 1))})
     for variant in TILES:
@@ -77,6 +86,7 @@ def test_adapters_per_block(n_ad):
 
 
 def _gated(w, tuning):
+    adapters = len(w.resident) > 0
     announce(f"glu direct {w.name} T={w.T} proj={w.proj[0]}")
     sess = Session(w)
     try:
@@ -85,7 +95,7 @@ def _gated(w, tuning):
         sess.bucket()
         out = sess.forward_glu(0, 1)
         torch.cuda.synchronize()
-        assert B.lora_last_launches(sess.ctx) == ["shrink", "expand_tiles", "gemm_glu_direct_256x256x64_w4"]
+        assert B.lora_last_launches(sess.ctx) == (["shrink", "expand_tiles"] if adapters else []) + ["gemm_glu_direct_256x256x64_w4"]
         h_ref = oracle.gated(w.x[0], w.W[0], w.W[1], w.token_ids, oracle.adapters_of(w, 0), oracle.adapters_of(w, 1))
         assert rel_err(bf16_tensor_to_bits(out), h_ref) <= TOL
     finally:
@@ -97,6 +107,11 @@ def test_gated_tiles(n_tokens, cols, ranks):
     rng = np.random.default_rng(cols)
     w = wl.custom("direct_glu", cols, [(192, cols), (192, cols)], ["gate", "up"], 6, 64, wl.BUCKET_RUNS, _runs(rng, n_tokens, 6, 60),
                   {i: ranks[i % len(ranks)] for i in range(6)})
+    _gated(w, TILES[0])
+
+
+def test_gated_tiles_without_a_resident_adapter():
+    w = wl.custom("direct_glu_base", 9, [(192, 520), (192, 520)], ["gate", "up"], 1, 8, wl.BUCKET_RUNS, np.full(300, -1, dtype=np.int32), {0: 8}, resident=[])
     _gated(w, TILES[0])
 
 
@@ -116,14 +131,20 @@ def test_automatic_choice(n_tokens, cols, gated, kernel):
     assert _launches(w, gated=gated) == ["shrink", "expand_tiles", kernel]
 
 
-def test_captured_launch_on_new_token_ids():
+@pytest.mark.parametrize("n_tokens", [1100, 300])
+@pytest.mark.parametrize("variant", TILES)
+def test_captured_launch_on_new_token_ids(variant, n_tokens):
+    # every replay has other ids: blocks of few, many and no adapters behind each other, so that what a replay before left in
+    # the expand's tables does not fit
     rng = np.random.default_rng(3)
-    w = wl.custom("direct_graph", 3, [(256, 1032)], ["p"], 6, 32, wl.BUCKET_SORTED, rng.integers(-1, 6, size=1100).astype(np.int32),
-                  {i: 8 << (i % 3) for i in range(6)})
-    sess = Session(w)
+    w = wl.custom("direct_graph", 3, [(256, 1032)], ["p"], 40, 32, wl.BUCKET_SORTED, rng.integers(-1, 40, size=n_tokens).astype(np.int32),
+                  {i: 8 << (i % 3) for i in range(40)})
+    sess = Session(w, path=B.LORA_PATH_FUSED)
     try:
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_FUSED_VARIANT, variant)
         sess.load(w.resident)
         sess.step()
+        assert B.lora_last_launches(sess.ctx) == _expected(variant)
         torch.cuda.synchronize()
         side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
@@ -133,8 +154,8 @@ def test_captured_launch_on_new_token_ids():
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g, stream=side):
             sess.step()
-        for rep in range(3):
-            ids = rng.integers(-1, 6 if rep != 1 else 1, size=w.T).astype(np.int32)
+        for rep, top in enumerate((40, 1, 40, 0, 6)):
+            ids = rng.integers(-1, top, size=w.T).astype(np.int32)
             sess.ids.copy_(torch.from_numpy(ids).to(sess.device))
             sess.out[0].zero_()
             torch.cuda.synchronize()
