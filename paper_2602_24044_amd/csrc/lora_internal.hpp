@@ -159,6 +159,7 @@ struct GemmArgs {
     int32_t shrink_front;
     int32_t front_expect;       // reports the tile workgroups wait for: shrink_front (one more in the host-forced test of the expired wait)
     int32_t wait_spins;         // polls of the bounded wait
+    int32_t turn;               // gemm_direct.hip: places by which the deal of the tiles turns from round to round
     int32_t k_rot;              // 64-wide-K kernels, fused path: column tiles start their walk over K at different places
     uint32_t* sync;
     uint32_t* flags;

@@ -62,6 +62,18 @@ def test_tile_edges(n_tokens, proj, mode, ranks, variant):
     _check(w, variant)
 
 
+@pytest.mark.parametrize("row_tiles,cols", [(2, 66568), (4, 33800), (6, 22400), (8, 16648), (16, 8456), (17, 8200), (32, 4360)])
+def test_every_tile_once_whatever_the_row_tiles(row_tiles, cols):
+    # two rounds and more of 256 x 256 tiles; from round to round the deal turns by 0, 1 or 8 places.  The last block of rows has
+    # twenty adapters, the others one or none
+    n_tokens = row_tiles * 256 - 3
+    ids = np.full(n_tokens, -1, dtype=np.int32)
+    ids[:n_tokens // 3] = 0
+    ids[-200:] = 1 + np.arange(200) // 10
+    w = wl.custom("direct_deal", row_tiles, [(192, cols)], ["p"], 21, 16, wl.BUCKET_RUNS, ids, {i: 16 if i % 2 else 8 for i in range(21)})
+    _check(w, TILES[0])
+
+
 @pytest.mark.parametrize("variant", TILES)
 def test_bias_and_packed_slices(variant):
     _check(wl.qwen_decode(shrink=8, n_tokens=300), variant, packed=True)
