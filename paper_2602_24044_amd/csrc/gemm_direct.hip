@@ -90,10 +90,13 @@ __device__ __forceinline__ float direct_silu(float z) { return z / (1.0f + __exp
 
 // ---------------------------------------------------------------------------------------------------
 // The expand as a continuation of the walk over K.  Per block of kDBlock grouped rows the adapters' ranks stand side by side,
-// in chunks of eight: record c of a block says which adapter (location, rank) and which eight of its ranks chunk c is, and
-// every row knows its own first chunk and how many it has.  Behind the last K tile the GEMM copies tiles of eight chunks: x
-// part = the row's scaled shrink results where a chunk is the row's own and zero elsewhere, W part = rows of that adapter's
-// B.  They are multiplied like any other K tile.  Adapters that come back later in a block have chunks of their own (RUNS).
+// in chunks of eight: record c of a block says which adapter (location, rank) and which eight of its ranks chunk c is and
+// which of the block's windows of kDB rows have it, and every row knows its own first chunk and how many it has.  Behind the
+// last K tile the GEMM copies tiles of eight chunks: x part = the row's scaled shrink results where a chunk is the row's own and
+// zero elsewhere, W part = rows of that adapter's B.  They are multiplied like any other K tile.  An adapter that comes back
+// later in a block (RUNS) has the chunks it had before: with chunks of its own for every run, 1100 tokens of four rank-64
+// adapters in turn were 256 expand tiles behind the 64 of the backbone (Llama-8B step 4032 us, now 1360; the register-staged
+// kernel 1460 - 1530).
 // ---------------------------------------------------------------------------------------------------
 constexpr int kDBlock = 256;
 
@@ -106,7 +109,9 @@ constexpr int kDShares = kDBlock / 32;
 constexpr int kDChunks = 4;                                   // shrink chunks per round of loads
 __global__ __launch_bounds__(kDBlock) void expand_tiles_kernel(GemmArgs a)
 {
-    __shared__ int s_wave[kDBlock / kWave];
+    __shared__ int s_wave[2][kDBlock / kWave];
+    __shared__ __attribute__((aligned(16))) int s_loc[kDBlock];   // per run: its adapter's location; behind the last: -1
+    __shared__ int s_same[kDBlock], s_first[kDBlock], s_windows[kDBlock];   // its adapter's first run; of such a run: first chunk, windows
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int T = a.dv.T, mr = a.dv.max_rank, m0 = (int)blockIdx.x * kDBlock, m = m0 + tid;
     if ((int)blockIdx.z == kDShares) {
@@ -116,33 +121,55 @@ __global__ __launch_bounds__(kDBlock) void expand_tiles_kernel(GemmArgs a)
         const int r = m < T && rl >= 0 ? rr : 0;
         const int loc = r > 0 ? rl : -1;
         const bool head = r > 0 && (tid == 0 || before != loc);
-        const int chunks = head ? r / 8 : 0;
+        // the row's run (rows without an adapter: any)
+        const unsigned long long heads = __ballot(head);
+        if (lane == 0) s_wave[0][wave] = __popcll(heads);
+        s_loc[tid] = -1;
+        s_windows[tid] = 0;
+        __syncthreads();
+        int run = __popcll(heads & ((2ull << lane) - 1ull)) - 1, runs = 0;
+#pragma unroll
+        for (int w = 0; w < kDBlock / kWave; ++w) {
+            if (w < wave) run += s_wave[0][w];
+            runs += s_wave[0][w];
+        }
+        if (run < 0) run = 0;
+        if (head) s_loc[run] = loc;
+        __syncthreads();
+        int same = run;                                      // the first run of the same adapter
+        if (a.ex.returns && head) {
+            for (int k = 0; k < runs; k += 4) {
+                const int4 o = *reinterpret_cast<const int4*>(s_loc + k);
+                if (o.w == loc && k + 3 < same) same = k + 3;
+                if (o.z == loc && k + 2 < same) same = k + 2;
+                if (o.y == loc && k + 1 < same) same = k + 1;
+                if (o.x == loc && k < same) same = k;
+            }
+        }
+        const int chunks = head && same == run ? r / 8 : 0;
         int v = chunks;
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
             const int o = __shfl_up(v, d, kWave);
             if (lane >= d) v += o;
         }
-        if (lane == kWave - 1) s_wave[wave] = v;
+        if (lane == kWave - 1) s_wave[1][wave] = v;
         __syncthreads();
-        int base = 0, all = 0;
+        int end = v, all = 0;                                // chunks up to and with this row's run
 #pragma unroll
         for (int w = 0; w < kDBlock / kWave; ++w) {
-            if (w < wave) base += s_wave[w];
-            all += s_wave[w];
+            if (w < wave) end += s_wave[1][w];
+            all += s_wave[1][w];
         }
-        const int end = base + v;                            // chunks up to and with this row's run
+        if (head) s_same[run] = same;
+        if (chunks > 0) s_first[run] = end - chunks;
+        __syncthreads();
+        const int own = r > 0 ? s_same[run] : 0;
+        if (r > 0 && (head || tid % kDB == 0)) atomicOr(&s_windows[own], 1 << (tid / kDB));
+        if (m < T) a.ex.row[m] = r > 0 ? s_first[own] | (r / 8) << 16 : 0;
+        __syncthreads();
         const size_t at = (size_t)blockIdx.x * kDBlock * (mr / 8);
-        for (int c = 0; c < chunks; ++c) a.ex.record[at + end - chunks + c] = int2{loc, r | (c * 8) << 8};
-        if (m < T) a.ex.row[m] = r > 0 ? (end - r / 8) | (r / 8) << 16 : 0;
-        int lo = r > 0 ? end - r / 8 : 0xffff, hi = r > 0 ? end : 0;
-#pragma unroll
-        for (int d = 1; d < kDB; d <<= 1) {
-            const int l = __shfl_xor(lo, d, kWave), u = __shfl_xor(hi, d, kWave);
-            lo = l < lo ? l : lo;
-            hi = u > hi ? u : hi;
-        }
-        if (m < T && tid % kDB == 0) a.ex.window[m / kDB] = hi > 0 ? lo | hi << 16 : 0;
+        for (int c = 0; c < chunks; ++c) a.ex.record[at + end - chunks + c] = int2{loc, r | (c * 8) << 8 | s_windows[run] << 16};
         if (tid == 0) a.ex.count[blockIdx.x] = all;
         if (tid < 4 && blockIdx.x == 0) a.ex.zero[tid] = 0;
         return;
@@ -276,7 +303,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
     // wave copies (8 XQ of them) the token and the chunks (ExpandTiles::row), the tokens of rows l and 64 + l of the wave's part of
     // the tile, record l % 8 of the block's chunks.
     struct Info {
-        int xtok, xrow, win, tok[MW];
+        int xtok, xrow, tok[MW];
         int2 rec;
     };
     auto load_info = [&](const Tile& t, Info& f, int lane) {
@@ -284,16 +311,12 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
         const int32_t* const perm = ka->dv.perm;
         const bool ex = ka->ex.on != 0;                      // uniform over the launch; otherwise nothing looks at these two
         const int32_t* const row = ex ? ka->ex.row : perm;
-        const int32_t* const window = ex ? ka->ex.window : perm;
         const int2* const rec = ex ? ka->ex.record + (size_t)(t.m0 / kDBlock) * kDBlock * (ka->dv.max_rank / 8) : reinterpret_cast<const int2*>(perm);
         int m = t.m0 + wave * (8 * XQ) + (lane & (8 * XQ - 1));
         if (m > T - 1) m = T - 1;
         f.xtok = perm[m];
         f.xrow = row[m];
         f.rec = rec[ex ? lane & 7 : 0];
-        int w0 = (t.m0 + wm * WTM) / kDB + lane % MB;
-        if (w0 > (T - 1) / kDB) w0 = (T - 1) / kDB;
-        f.win = window[w0];
 #pragma unroll
         for (int k = 0; k < MW; ++k) {
             int mk = t.m0 + wm * WTM + k * kWave + lane;
@@ -464,6 +487,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
         load_info(after.on ? after : cur, info_after, lr);
         const int nl_after = expand_tiles(after);
         const u32x4 xrs_after = x_buffer(after), wrs_after = w_buffer(after, false), urs_after = GLU ? w_buffer(after, true) : wrs_after;
+        int users = 0, users_next = 0;                       // per lane: windows that have chunk l % 8 of K tile j and of the next one
         auto last_tile = [&](int j, auto expand_c) __attribute__((always_inline)) {
             constexpr bool EXPAND = decltype(expand_c)::value;   // K tile j is one of the expand's
             const int l = j + 2 - nk;                        // the tile to copy: of the expand, while below nl
@@ -496,8 +520,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
                 for (int o = 0; o < 2; ++o) {
                     const int c = chunk_of(o * 8 + (ln >> 3), ln);
                     const int loc = __shfl(info.rec.x, c, kWave), rr = __shfl(info.rec.y, c, kWave);
-                    const uint32_t rank = (uint32_t)(rr & 0xff);
-                    const uint8_t* const at = reinterpret_cast<const uint8_t*>(ka->dv.slots + (size_t)(uint32_t)loc * kLocUnit + (size_t)rank * ka->g.s[GLU ? p : cur.si].b_unit + (rr >> 8));
+                    const uint32_t rank = (uint32_t)(rr & 0xff), from_rank = (uint32_t)(rr >> 8) & 0xffu;
+                    const uint8_t* const at = reinterpret_cast<const uint8_t*>(ka->dv.slots + (size_t)(uint32_t)loc * kLocUnit + (size_t)rank * ka->g.s[GLU ? p : cur.si].b_unit + from_rank);
 #pragma unroll
                     for (int up = 0; up < 2; ++up) {
                         const bool on = c8 + c < chunks && (!GLU || up == p);
@@ -533,15 +557,14 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
             } else {
                 // The same steps without an order of their own.  A window of 16 rows takes the chunks its own rows use and no
                 // others, whatever these hold (their x part is zero, but zero times infinity is not).
-                const int c0 = (GLU ? (j - nk) >> 1 : j - nk) * 8;
+                const int window0 = (cur.m0 % kDBlock + wm * WTM) / kDB;
                 auto multiply = [&](auto fc) __attribute__((always_inline)) {
                     constexpr int f = decltype(fc)::value;
-                    const int s0 = c0 + f * 4, c = s0 + (ln >> 4);
+                    const uint32_t mine = (uint32_t)__shfl(users, f * 4 + (ln >> 4), kWave) >> (16 + window0);
                     direct_for<MB>([&](auto wc) {
                         constexpr int w = decltype(wc)::value;
-                        const int win = __builtin_amdgcn_readlane(info.win, w), lo = win & 0xffff, hi = win >> 16;
-                        if (lo < s0 + 4 && s0 < hi) {          // uniform over the wave
-                            const bool own = c >= lo && c < hi;
+                        const bool own = (mine >> w & 1u) != 0u;
+                        if (__builtin_amdgcn_ballot_w64(own) != 0) {
 #pragma unroll
                             for (int nb = 0; nb < NB; ++nb) {
                                 const u32x4 v = own ? __builtin_bit_cast(u32x4, Fw[f][nb]) : u32x4{0u, 0u, 0u, 0u};
@@ -560,6 +583,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
                 multiply(std::integral_constant<int, 1>{});
                 rotate();
             }
+            users = users_next;
+            users_next = info.rec.y;
         };
 #pragma clang loop unroll(disable)
         for (int j = nk - 2; j < nk; ++j) last_tile(j, std::false_type{});

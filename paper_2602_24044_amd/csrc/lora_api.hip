@@ -148,7 +148,6 @@ size_t place_expand_tiles(ExpandTiles& ex, char* at, int n, int32_t T, int32_t m
     auto take = [&](size_t bytes) { char* p = at + o; o = align_up(o + bytes, kAlign); return p; };
     ex.count = reinterpret_cast<int32_t*>(take(4 * blocks));
     ex.row = reinterpret_cast<int32_t*>(take(4 * (size_t)T));
-    ex.window = reinterpret_cast<int32_t*>(take(4 * (((size_t)T + 15) / 16)));
     ex.record = reinterpret_cast<int2*>(take(8 * blocks * 256 * (size_t)(max_rank / 8)));
     ex.zero = reinterpret_cast<int32_t*>(take(16));
     ex.v = reinterpret_cast<uint16_t*>(take(2 * (size_t)n * (size_t)T * (size_t)max_rank));
@@ -1318,6 +1317,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         a.ex.on = 0;
         if (fused_direct(fv) && sa.on) {
             a.ex.on = 1;
+            a.ex.returns = seg->mode != LORA_BUCKET_SORTED ? 1 : 0;
             place_expand_tiles(a.ex, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank);
             LaunchScope ls(c, s, "expand_tiles");
             if (HIP_FAIL(launch_expand_tiles(a, s))) return LORA_ERR_HIP;

@@ -126,11 +126,11 @@ struct ShrinkArgs {
 // launch in front of it into scratch of the call.
 struct ExpandTiles {
     int32_t on;          // 0: no adapter resident, nothing to expand
-    int32_t pad_;
+    int32_t returns;     // an adapter may come back within a block (RUNS)
     int32_t* count;      // [blocks of 256 rows] chunks of eight ranks in the block
     int32_t* row;        // [T] first chunk of the row's adapter in its block | chunks << 16
-    int32_t* window;     // [T / 16, rounded up] first chunk of the window's rows | end << 16 (0: none)
-    int2* record;        // [blocks][256 max_rank / 8] location of the adapter, its rank | first of the chunk's ranks << 8
+    int2* record;        // [blocks][256 max_rank / 8] location of the adapter, its rank | first of the chunk's ranks << 8 |
+                         // the block's windows of 16 rows that have it << 16
     int32_t* zero;       // [4] zeros
     uint16_t* v;         // [slices][T][max_rank] bf16: scaled shrink results
 };

@@ -127,6 +127,62 @@ def test_gated_tiles_without_a_resident_adapter():
     _gated(w, TILES[0])
 
 
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("n_tokens,n_ad,rank,order", [
+    (300, 4, 64, "turns"),                                # every row a run of its own, four adapters per block
+    (513, 150, 16, "random"),                             # runs of one and two rows; most adapters come back
+    (260, 256, 8, "turns"),                               # 256 runs in a block and none comes back; four come back in the next
+    (512, 3, 64, "palindrome"),                           # 0 1 2 1 0, runs that cross the windows of 16 rows
+])
+def test_adapters_that_come_back(n_tokens, n_ad, rank, order, gated):
+    rng = np.random.default_rng(n_ad)
+    if order == "turns":
+        ids = np.arange(n_tokens) % n_ad
+    elif order == "palindrome":
+        ids = np.repeat([0, 1, -1, 2, 1, 0], 37)
+        ids = np.tile(ids, n_tokens // len(ids) + 1)[:n_tokens]
+    else:
+        ids = np.repeat(rng.integers(-1, n_ad, size=n_tokens), rng.integers(1, 3, size=n_tokens))[:n_tokens]
+    proj = [(256, 264)] * (2 if gated else 1)
+    w = wl.custom("direct_back", n_tokens, proj, ["gate", "up"][:len(proj)], n_ad, 64, wl.BUCKET_RUNS, ids.astype(np.int32), {i: rank if i % 5 else 8 for i in range(n_ad)})
+    if gated:
+        _gated(w, TILES[0])
+    else:
+        for variant in TILES:
+            _check(w, variant)
+
+
+def _gemm_ms(w, variant):
+    sess = Session(w, path=B.LORA_PATH_FUSED)
+    try:
+        B.lora_set_tuning(sess.ctx, B.LORA_TUNE_FUSED_VARIANT, variant)
+        sess.load(w.resident)
+        sess.bucket()
+        for _ in range(3):
+            sess.forward(0)
+        torch.cuda.synchronize()
+        B.lora_profile_enable(sess.ctx, True)
+        for _ in range(20):
+            sess.forward(0)
+        torch.cuda.synchronize()
+        ms, count = B.lora_profile_collect(sess.ctx)["gemm_fused_" + NAMES[TILES.index(variant)]]
+        return ms / count
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("variant", TILES)
+def test_adapters_that_come_back_are_expanded_once(variant):
+    # the same four adapters of rank 64 token by token and as one prompt each: four K tiles of expand per block against one or two,
+    # behind sixteen.  A K tile per run would be 256 of them
+    ms = []
+    for ids in (np.arange(1024) // 256, np.arange(1024) % 4):
+        w = wl.custom("direct_once", 1, [(1024, 1024)], ["p"], 4, 64, wl.BUCKET_RUNS, ids.astype(np.int32), {i: 64 for i in range(4)})
+        ms.append(_gemm_ms(w, variant))
+    announce(f"one prompt each {ms[0] * 1e3:.1f} us, in turns {ms[1] * 1e3:.1f} us")
+    assert ms[1] < 3.0 * ms[0]
+
+
 @pytest.mark.parametrize("n_tokens,cols,gated,kernel", [
     (1300, 4096, False, "gemm_fused_direct_128x256x64_w4"),
     (2100, 4104, False, "gemm_fused_direct_256x192x64_w4"),
@@ -201,3 +257,28 @@ def test_values_that_are_not_finite_stay_with_their_adapter(variant):
     assert bool(torch.isfinite(clean).all())
     assert not bool(torch.isfinite(poisoned[48:96]).any())
     assert torch.equal(clean[:48], poisoned[:48]) and torch.equal(clean[96:], poisoned[96:])
+
+
+@pytest.mark.parametrize("variant", TILES)
+def test_values_that_are_not_finite_of_an_adapter_that_comes_back(variant):
+    # adapters 0, 1, 0, 2, 1, 0 of three windows each in a block, adapter 1 with an infinity: its chunks lie between the others'
+    ids = np.repeat(np.array([0, 1, 0, 2, 1, 0], dtype=np.int32), 48)
+    w = wl.custom("direct_inf_back", 1, [(192, 264)], ["p"], 3, 16, wl.BUCKET_RUNS, ids, {0: 16, 1: 16, 2: 8})
+    outs = []
+    for poison in (False, True):
+        if poison:
+            w.adapters[1].B[0][:, 3] = 0x7f80
+        sess = Session(w, path=B.LORA_PATH_FUSED)
+        try:
+            B.lora_set_tuning(sess.ctx, B.LORA_TUNE_FUSED_VARIANT, variant)
+            sess.load(w.resident)
+            sess.bucket()
+            outs.append(sess.forward(0).clone())
+            torch.cuda.synchronize()
+        finally:
+            sess.close()
+    clean, poisoned = outs
+    mine = torch.from_numpy(ids == 1).to(clean.device)
+    assert bool(torch.isfinite(clean).all())
+    assert not bool(torch.isfinite(poisoned[mine]).any())
+    assert torch.equal(clean[~mine], poisoned[~mine])
