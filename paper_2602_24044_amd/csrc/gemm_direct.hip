@@ -109,7 +109,7 @@ constexpr int kDShares = kDBlock / 32;
 constexpr int kDChunks = 4;                                   // shrink chunks per round of loads
 __global__ __launch_bounds__(kDBlock) void expand_tiles_kernel(GemmArgs a)
 {
-    __shared__ int s_wave[2][kDBlock / kWave];
+    __shared__ int s_wave[2][kDBlock / kWave], s_range[kDBlock / kWave];
     __shared__ __attribute__((aligned(16))) int s_loc[kDBlock];   // per run: its adapter's location; behind the last: -1
     __shared__ int s_same[kDBlock], s_first[kDBlock], s_windows[kDBlock];   // its adapter's first run; of such a run: first chunk, windows
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -166,8 +166,23 @@ __global__ __launch_bounds__(kDBlock) void expand_tiles_kernel(GemmArgs a)
         __syncthreads();
         const int own = r > 0 ? s_same[run] : 0;
         if (r > 0 && (head || tid % kDB == 0)) atomicOr(&s_windows[own], 1 << (tid / kDB));
-        if (m < T) a.ex.row[m] = r > 0 ? s_first[own] | (r / 8) << 16 : 0;
+        const int first = r > 0 ? s_first[own] : 0xffff;
+        if (m < T) a.ex.row[m] = r > 0 ? first | (r / 8) << 16 : 0;
+        int lo = first, hi = r > 0 ? first + r / 8 : 0;      // chunks of the wave's rows
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int l = __shfl_xor(lo, d, kWave), u = __shfl_xor(hi, d, kWave);
+            lo = l < lo ? l : lo;
+            hi = u > hi ? u : hi;
+        }
+        if (lane == 0) s_range[wave] = lo | hi << 16;
         __syncthreads();
+        if (tid < 2) {
+            const int o = s_range[2 * tid], p = s_range[2 * tid + 1];
+            lo = (o & 0xffff) < (p & 0xffff) ? o & 0xffff : p & 0xffff;
+            hi = o >> 16 > p >> 16 ? o >> 16 : p >> 16;
+            a.ex.half[2 * blockIdx.x + tid] = hi > 0 ? (lo & ~7) | hi << 16 : 0;
+        }
         const size_t at = (size_t)blockIdx.x * kDBlock * (mr / 8);
         for (int c = 0; c < chunks; ++c) a.ex.record[at + end - chunks + c] = int2{loc, r | (c * 8) << 8 | s_windows[run] << 16};
         if (tid == 0) a.ex.count[blockIdx.x] = all;
@@ -301,12 +316,12 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
     }
     // What the copies and the epilogue of one output tile need; loaded two tiles ahead.  Per lane: of row l of the rows the
     // wave copies (8 XQ of them) the token and the chunks (ExpandTiles::row), the tokens of rows l and 64 + l of the wave's part of
-    // the tile, record l % 8 of the block's chunks.
+    // the tile, record l % 8 of the tile's chunks.
     struct Info {
         int xtok, xrow, tok[MW];
         int2 rec;
     };
-    auto load_info = [&](const Tile& t, Info& f, int lane) {
+    auto load_info = [&](const Tile& t, Info& f, int lane, int first_chunk) {
         const ArgsInPlace ka = args_in_place();
         const int32_t* const perm = ka->dv.perm;
         const bool ex = ka->ex.on != 0;                      // uniform over the launch; otherwise nothing looks at these two
@@ -316,7 +331,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
         if (m > T - 1) m = T - 1;
         f.xtok = perm[m];
         f.xrow = row[m];
-        f.rec = rec[ex ? lane & 7 : 0];
+        f.rec = rec[ex ? first_chunk + (lane & 7) : 0];
 #pragma unroll
         for (int k = 0; k < MW; ++k) {
             int mk = t.m0 + wm * WTM + k * kWave + lane;
@@ -324,12 +339,17 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
             f.tok[k] = perm[mk];
         }
     };
-    // K tiles of the expand behind the backbone's
-    auto expand_tiles = [&](const Tile& t) {
+    // The chunks that the rows of the tile use: the first (a multiple of eight) | the end << 16, and the K tiles of the expand
+    // that they take behind the backbone's.  128 rows go through those between their first and their last adapter's only: with
+    // all of the block's, a launch of one round whose last rows are a hundred one-token requests ends with them (1300 tokens, 128
+    // adapters of 8 to 64 ranks, Llama-8B o: 112 -> 91 us; down 238 -> 206).
+    auto expand_chunks = [&](const Tile& t) {
         const ArgsInPlace ka = args_in_place();
         if (!t.on || !ka->ex.on) return 0;
-        return (__builtin_amdgcn_readfirstlane(ka->ex.count[t.m0 / kDBlock]) + 7) / 8 * (GLU ? 2 : 1);
+        return BM == kDBlock ? __builtin_amdgcn_readfirstlane(ka->ex.count[t.m0 / kDBlock]) << 16 : __builtin_amdgcn_readfirstlane(ka->ex.half[t.m0 / (kDBlock / 2)]);
     };
+    static_assert(BM == kDBlock || BM == kDBlock / 2, "a block or half of one");
+    auto expand_tiles = [](int chunks) { return ((chunks >> 16) - (chunks & 0xffff) + 7) / 8 * (GLU ? 2 : 1); };
     auto x_buffer = [&](const Tile& t) {
         const ArgsInPlace ka = args_in_place();
         return buffer_of(ka->g.s[t.si].x, t.on ? (uint32_t)ka->dv.T * (uint32_t)K * 2u : 0u);
@@ -379,7 +399,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
             asm volatile("" : "+v"(xoff[q]));
         }
     };
-    load_info(cur, info, lane);
+    int chunks = expand_chunks(cur);
+    load_info(cur, info, lane, chunks & 0xffff);
     u32x4 xrs = x_buffer(cur), wrs = w_buffer(cur, false), urs = GLU ? w_buffer(cur, true) : wrs;
     u32x4 xrs_next, wrs_next, urs_next;
     x_offsets(info, lane);
@@ -405,8 +426,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
     direct_for<WQ>([&](auto q) { copy_w(q, WST); });
     direct_for<XQ>([&](auto q) { copy_x(q, XST); });
     Tile nxt = next_tile();
-    load_info(nxt.on ? nxt : cur, info_next, lane);
-    int nl = expand_tiles(cur), nl_next = expand_tiles(nxt);
+    int chunks_next = expand_chunks(nxt);
+    load_info(nxt.on ? nxt : cur, info_next, lane, chunks_next & 0xffff);
     xrs_next = x_buffer(nxt);
     wrs_next = w_buffer(nxt, false);
     urs_next = GLU ? w_buffer(nxt, true) : wrs_next;
@@ -437,7 +458,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
     bool stored = false;                                     // kStores stores stand behind the copies of K tile 1
 
     for (;;) {
-        const int nkt = nk + nl;                             // K tiles of this output tile
+        const int nl = expand_tiles(chunks), nkt = nk + nl;  // K tiles of this output tile
         // K tile j.  While it is multiplied, W of tile j + 2 is copied into the third W stage and, behind the barrier that
         // says every wave has its last fragments, x of tile j + 2 into the stage of tile j.  The walk over K goes on into the
         // expand's tiles and into the workgroup's next output tile.
@@ -484,8 +505,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
         if (nxt.on) after = next_tile();
         int lr = lane;
         asm volatile("" : "+v"(lr));
-        load_info(after.on ? after : cur, info_after, lr);
-        const int nl_after = expand_tiles(after);
+        const int chunks_after = expand_chunks(after);
+        load_info(after.on ? after : cur, info_after, lr, chunks_after & 0xffff);
         const u32x4 xrs_after = x_buffer(after), wrs_after = w_buffer(after, false), urs_after = GLU ? w_buffer(after, true) : wrs_after;
         int users = 0, users_next = 0;                       // per lane: windows that have chunk l % 8 of K tile j and of the next one
         auto last_tile = [&](int j, auto expand_c) __attribute__((always_inline)) {
@@ -495,7 +516,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
             int ln = lane;
             asm volatile("" : "+v"(ln));
             const ArgsInPlace ka = args_in_place();
-            const int mr = ka->dv.max_rank, p = GLU ? l & 1 : 0, c8 = (GLU ? l >> 1 : l) * 8;
+            const int mr = ka->dv.max_rank, p = GLU ? l & 1 : 0, c8 = (chunks & 0xffff) + (GLU ? l >> 1 : l) * 8;
             // W copies of either kind have a first row, a distance between rows and a place in the row per lane, for even and
             // for odd copies (whose chunk positions differ by four); [1]: of the matrix `up`
             const Tile of = ex || !nxt.on ? cur : nxt;
@@ -514,8 +535,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
                     xoff[q] = own ? (uint32_t)((cur.m0 + r) * mr + d * 8) * 2u : kNowhere;
                     asm volatile("" : "+v"(xoff[q]));
                 }
-                if (c8 > 0 && p == 0) info.rec = ka->ex.record[(size_t)(cur.m0 / kDBlock) * kDBlock * (mr / 8) + c8 + (ln & 7)];
-                const int chunks = __builtin_amdgcn_readfirstlane(ka->ex.count[cur.m0 / kDBlock]);
+                if (l > 0 && p == 0) info.rec = ka->ex.record[(size_t)(cur.m0 / kDBlock) * kDBlock * (mr / 8) + c8 + (ln & 7)];
+                const int end = chunks >> 16;
 #pragma unroll
                 for (int o = 0; o < 2; ++o) {
                     const int c = chunk_of(o * 8 + (ln >> 3), ln);
@@ -524,7 +545,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
                     const uint8_t* const at = reinterpret_cast<const uint8_t*>(ka->dv.slots + (size_t)(uint32_t)loc * kLocUnit + (size_t)rank * ka->g.s[GLU ? p : cur.si].b_unit + from_rank);
 #pragma unroll
                     for (int up = 0; up < 2; ++up) {
-                        const bool on = c8 + c < chunks && (!GLU || up == p);
+                        const bool on = c8 + c < end && (!GLU || up == p);
                         from[up][o] = on ? at : reinterpret_cast<const uint8_t*>(ka->ex.zero);
                         pitch[up][o] = on ? rank * 2u : 0u;
                     }
@@ -624,8 +645,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
             row_off[k] = mw0 + k * kWave + ln < T ? (uint32_t)info.tok[k] * (uint32_t)N * 2u : kNowhere;
         cur = nxt;
         nxt = after;
-        nl = nl_next;
-        nl_next = nl_after;
+        chunks = chunks_next;
+        chunks_next = chunks_after;
         __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0): the data of the tile after the next
         info = info_next;
         info_next = info_after;

@@ -147,6 +147,7 @@ size_t place_expand_tiles(ExpandTiles& ex, char* at, int n, int32_t T, int32_t m
     size_t o = 0;
     auto take = [&](size_t bytes) { char* p = at + o; o = align_up(o + bytes, kAlign); return p; };
     ex.count = reinterpret_cast<int32_t*>(take(4 * blocks));
+    ex.half = reinterpret_cast<int32_t*>(take(8 * blocks));
     ex.row = reinterpret_cast<int32_t*>(take(4 * (size_t)T));
     ex.record = reinterpret_cast<int2*>(take(8 * blocks * 256 * (size_t)(max_rank / 8)));
     ex.zero = reinterpret_cast<int32_t*>(take(16));

@@ -128,6 +128,7 @@ struct ExpandTiles {
     int32_t on;          // 0: no adapter resident, nothing to expand
     int32_t returns;     // an adapter may come back within a block (RUNS)
     int32_t* count;      // [blocks of 256 rows] chunks of eight ranks in the block
+    int32_t* half;       // [2 blocks] of 128 rows of a block: the first chunk they use, rounded down to eight | the end << 16
     int32_t* row;        // [T] first chunk of the row's adapter in its block | chunks << 16
     int2* record;        // [blocks][256 max_rank / 8] location of the adapter, its rank | first of the chunk's ranks << 8 |
                          // the block's windows of 16 rows that have it << 16

@@ -183,6 +183,29 @@ def test_adapters_that_come_back_are_expanded_once(variant):
     assert ms[1] < 3.0 * ms[0]
 
 
+def test_128_rows_take_their_own_adapters_of_the_block():
+    # 256 rows of 128 adapters of rank 64: sorted, each half of the block has 64 of them (64 K tiles behind three), in turns both
+    # have all
+    ms = []
+    for ids in (np.repeat(np.arange(128), 2), np.arange(256) % 128):
+        w = wl.custom("direct_half", 1, [(192, 1024)], ["p"], 128, 64, wl.BUCKET_RUNS, ids.astype(np.int32), {i: 64 for i in range(128)})
+        ms.append(_gemm_ms(w, B.FUSED_VARIANTS["direct_128x256x64_w4"]))
+    announce(f"sorted {ms[0] * 1e3:.1f} us, in turns {ms[1] * 1e3:.1f} us")
+    assert ms[0] < 0.75 * ms[1]
+
+
+@pytest.mark.parametrize("n_tokens,order", [(400, "sorted"), (256, "sorted"), (390, "back")])
+def test_128_rows_of_a_block(n_tokens, order):
+    # halves whose first chunk is not a multiple of eight, without an adapter, and (RUNS) with an adapter of the other half
+    if order == "sorted":
+        ids = np.sort(np.random.default_rng(7).integers(-1, 90, size=n_tokens))
+        ids[:40] = -1
+    else:
+        ids = np.concatenate([np.repeat(np.arange(13), 10)[:128], np.full(100, -1), np.repeat([5, 20, 11], 40), np.full(42, 20)])
+    w = wl.custom("direct_half", n_tokens, [(256, 264)], ["p"], 90, 64, wl.BUCKET_RUNS, ids.astype(np.int32), {i: (8, 24, 64)[i % 3] for i in range(90)})
+    _check(w, B.FUSED_VARIANTS["direct_128x256x64_w4"])
+
+
 @pytest.mark.parametrize("n_tokens,cols,gated,kernel", [
     (1300, 4096, False, "gemm_fused_direct_128x256x64_w4"),
     (2100, 4104, False, "gemm_fused_direct_256x192x64_w4"),
