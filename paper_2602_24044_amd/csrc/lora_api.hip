@@ -1180,13 +1180,20 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                    !over_byte_offsets((uint64_t)plan.n_max, K) &&
                    (!sa.on || place_expand_tiles(probe, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank) <= scr.part_elems * 4);
         }();
-        // The expand of a 256-row block takes a K tile per 64 ranks of its adapters (2.5 us each, in the register-staged kernel's
-        // epilogue 1.8).  Where a batch is spread so thinly over so many adapters that these outnumber 0.4 of the backbone's K
-        // tiles, that kernel is the faster one: Llama-8B gate|up, 512 tokens of 285 adapters of 30 ranks each, 70 tiles behind 64:
-        // 238 us against 278.  Estimated from the adapters that are resident, evenly spread.
+        // The expand of a 256-row block takes a K tile per 64 ranks of its adapters (gated: two), each as long as one and a quarter
+        // of the backbone's; in the epilogue of the register-staged kernel it takes its time by adapters, not ranks, and that
+        // kernel is the faster one where a batch is spread so thinly over so many adapters that their ranks reach about half of K.
+        // Estimated from the adapters that are resident, evenly spread.  Whole steps, sorted, staged /
+        // copied (block's ranks, gated ones doubled): Llama-8B 1024 tokens of 384 adapters (0.44 K) 836 / 820 us, 512 of 150
+        // (0.56 K) 554 / 561, 512 of 285 (1.05 K) 657 / 681; Qwen2.5-7B 1024 of 200 (0.43 K) 985 / 936, 640 of 200 (0.68 K) 763 /
+        // 830.  Gated, several rounds: Llama-8B 1500 of 128 (0.33 K) 1042 / 1000, 4000 of 384 (0.38 K) 2270 / 2167, 2048 of 384 (0.45 K)
+        // 1176 / 1292.  Gated, up to two rounds, where the rows of the last block count for more: Llama-8B 1024 of 128 (0.30 K)
+        // 698 / 690, 777 of 65 (0.33 K) 739 / 758, 1024 of 200 (0.46 K) 740 / 759.
+        const bool sorted = seg->mode == LORA_BUCKET_SORTED;
         const double blocks = std::max(1.0, (double)T / 256.0);
-        const double block_ranks = (glu ? 2.0 : 1.0) * (double)c->ranks_resident / std::max(1, c->n_resident) * std::min(256.0, 1.0 + c->n_resident / blocks);
-        const bool direct = direct_ok && (!sa.on || block_ranks <= 0.4 * K);
+        const double ranks_each = (glu ? 2.0 : 1.0) * (double)c->ranks_resident / std::max(1, c->n_resident);
+        const bool two_rounds = tiles_of(256, 256) <= 2L * c->n_cus;      // gate's and up's columns together, gated too
+        const bool direct = direct_ok && (!sa.on || ranks_each * std::min(256.0, 1.0 + c->n_resident / blocks) <= (!glu ? 0.45 : two_rounds ? 0.32 : 0.4) * K);
         // Up to 64 tokens the tile has 32 or 64 rows; with more such tiles than CUs, the variant of which two workgroups
         // share a CU.
         auto small_variant = [&](int one, int pair, long tiles) { return tiles <= c->n_cus ? one : pair; };
@@ -1278,7 +1285,19 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             }
         }
         if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)plan.n_max, K)) && !fused_wide_k(fv, glu)) fv = glu ? 8 : 10;
+        const bool auto_direct = fused_direct(fv) && c->tune[LORA_TUNE_FUSED_VARIANT] == 0;
         if (fused_direct(fv) && !direct_ok) fv = 0;
+        if (auto_direct && fused_direct(fv) && sa.on) {
+            // the staged tiles of the same shape
+            const int staged = fv == kDirect192 ? kStaged192 : fv == kDirect128 ? kStaged128 : 0;
+            const int rows = fv == kDirect128 ? 128 : 256, cols = fv == kDirect192 ? 192 : 256;
+            const double at_most = ranks_each * std::min<double>(rows, c->n_resident);
+            if (sorted && tiles_of(rows, cols) <= c->n_cus && at_most > 0.5 * K) {
+                // A single round ends with the tile that has the most, and the rows of a mixed step's one-token requests have
+                // nearly all there are: 1300 tokens, 650 of them of 128 adapters of 8 to 64 ranks, Llama-8B q|k|v 154 us, staged 119.
+                fv = staged;
+            }
+        }
         const bool use_tail = auto_variant && (fv == 0 || fv == kDirect) && m_full < T;
         const int m_split = use_tail ? m_full : T;
         // Small batches leave CUs without a tile (224 tiles of 256 x 128 for a Llama-8B gate|up, 198 of 256 x 192
@@ -1318,7 +1337,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         a.ex.on = 0;
         if (fused_direct(fv) && sa.on) {
             a.ex.on = 1;
-            a.ex.returns = seg->mode != LORA_BUCKET_SORTED ? 1 : 0;
+            a.ex.returns = sorted ? 0 : 1;
             place_expand_tiles(a.ex, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank);
             LaunchScope ls(c, s, "expand_tiles");
             if (HIP_FAIL(launch_expand_tiles(a, s))) return LORA_ERR_HIP;

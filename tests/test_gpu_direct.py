@@ -222,6 +222,50 @@ def test_automatic_choice(n_tokens, cols, gated, kernel):
     assert _launches(w, gated=gated) == ["shrink", "expand_tiles", kernel]
 
 
+STAGED = {"gemm_fused_direct_128x256x64_w4": "gemm_fused_staged_128x256x64_w8", "gemm_fused_direct_256x192x64_w4": "gemm_fused_staged_256x192x64_w8",
+          "gemm_fused_direct_256x256x64_w4": "gemm_fused_staged_256x256x64_w8", "gemm_glu_direct_256x256x64_w4": "gemm_glu_staged_256x256x64_w8"}
+
+
+@pytest.mark.parametrize("n_tokens,cols,gated,most,kernel", [
+    # sorted, several rounds: 8 (1 + adapters / blocks) ranks of at most 0.45 of K = 192, gated twice as many of at most 0.4
+    (2049, 28680, False, 78, "gemm_fused_direct_256x256x64_w4"),
+    (1025, 18944, True, 15, "gemm_glu_direct_256x256x64_w4"),
+    # a single round: 8 (gated 16) ranks of every adapter, of at most 0.5 of K
+    (1300, 4096, False, 12, "gemm_fused_direct_128x256x64_w4"),
+    (2100, 4104, False, 12, "gemm_fused_direct_256x192x64_w4"),
+    (1025, 2048, True, 6, "gemm_glu_direct_256x256x64_w4"),
+])
+def test_sorted_batches_of_many_adapters_take_the_staged_tiles(n_tokens, cols, gated, most, kernel):
+    proj = [(192, cols)] * (2 if gated else 1)
+    for n_ad in (most, most + 1):
+        ids = (np.arange(n_tokens) % n_ad).astype(np.int32)
+        w = wl.custom("direct_many", 4, proj, ["gate", "up"][:len(proj)], n_ad, 8, wl.BUCKET_SORTED, ids, {i: 8 for i in range(n_ad)})
+        assert _launches(w, gated=gated) == (["shrink", "expand_tiles", kernel] if n_ad == most else ["shrink", STAGED[kernel]]), n_ad
+
+
+@pytest.mark.parametrize("max_rank,kernels", [(8, ["shrink", "expand_tiles", "gemm_fused_direct_128x256x64_w4"]),
+                                              (64, ["shrink", "gemm_fused_staged_128x256x64_w8"])])
+def test_expand_tables_that_do_not_fit_the_scratch(max_rank, kernels):
+    # 20000 rows of bf16 shrink results, 0.3 or 2.6 MB, beside the tables in 1 MB of scratch for partial tiles
+    w = wl.custom("direct_scratch", 4, [(192, 256)], ["p"], 2, max_rank, wl.BUCKET_RUNS, np.repeat([0, 1], 10000).astype(np.int32), {0: 8, 1: max_rank})
+    sess = Session(w, split_k=1)
+    try:
+        sess.load(w.resident)
+        sess.bucket()
+        out = sess.forward(0)
+        assert B.lora_last_launches(sess.ctx) == kernels
+        y_ref = oracle.project(w.x[0], w.W[0], w.token_ids, oracle.adapters_of(w, 0))
+        assert rel_err(bf16_tensor_to_bits(out), y_ref) <= TOL
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("n_tokens,kernel", [(65532, "gemm_fused_direct_256x256x64_w4"), (65536, "gemm_fused_staged_256x256x64_w8")])
+def test_output_of_four_gigabytes(n_tokens, kernel):
+    w = wl.custom("direct_4g", 4, [(192, 32768)], ["p"], 1, 8, wl.BUCKET_RUNS, np.full(n_tokens, -1, dtype=np.int32), {0: 8}, resident=[])
+    assert _launches(w) == [kernel]
+
+
 @pytest.mark.parametrize("n_tokens", [1100, 300])
 @pytest.mark.parametrize("variant", TILES)
 def test_captured_launch_on_new_token_ids(variant, n_tokens):
