@@ -450,4 +450,15 @@ __device__ inline void expand_windows(f32x16 (&acc)[MB][NB], const int (&slot)[M
     }
 }
 
+// More chunks of ranks in the launch's blocks than the host set as the limit (ExpandTiles::long_chunks).  The same for every wave.
+__device__ inline bool expand_is_long(const GemmArgs& a)
+{
+    const int blocks = (a.dv.T + 255) / 256;
+    int n = 0;
+    for (int b = threadIdx.x & (kWave - 1); b < blocks; b += kWave) n += a.ex.count[b];
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) n += __shfl_xor(n, d, kWave);
+    return __builtin_amdgcn_readfirstlane(n) > a.ex.long_chunks;
+}
+
 }  // namespace lora

@@ -253,7 +253,8 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
     const int i = lane & 15, h = lane >> 4;
     const int wm = wave & 1, wn = wave >> 1;
     const int T = a.m_end, K = a.K;                         // rows past m_end are computed, never stored
-    const int nk = K / kDK;                                 // at least 2 (host)
+    const int nk = K / kDK;                                 // at least 3 (host): K tile 0 and the last two are not the same ones
+    if (a.ex.long_chunks > 0 && expand_is_long(a)) return;  // uniform over the launch: the other kernel's
 
     // ---- the tiles of this workgroup ----
     // Consecutive workgroups go to different XCDs.  Row tile fastest; with up to kDXcdRuns row tiles every XCD takes a

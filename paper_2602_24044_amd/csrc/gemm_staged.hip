@@ -76,6 +76,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_staged_kernel(GemmArgs a
     const int i = lane & 31, h = lane >> 5;
     const int wm = wave % WGM, wn = wave / WGM;
     const int T = a.m_end, K = a.K;                         // rows past m_end are computed, never stored
+    if (a.ex.long_chunks > 0 && !expand_is_long(a)) return; // uniform over the launch: gemm_direct_kernel has done it
 
     // blockIdx -> (tile_m, tile_n): the M tile is the fastest index (neighbouring workgroups share the W tile).
     // Consecutive workgroups go to different XCDs: with up to kXcdRuns row tiles every XCD takes a contiguous run of the

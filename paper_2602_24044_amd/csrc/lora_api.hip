@@ -1183,17 +1183,19 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         // The expand of a 256-row block takes a K tile per 64 ranks of its adapters (gated: two), each as long as one and a quarter
         // of the backbone's; in the epilogue of the register-staged kernel it takes its time by adapters, not ranks, and that
         // kernel is the faster one where a batch is spread so thinly over so many adapters that their ranks reach about half of K.
-        // Estimated from the adapters that are resident, evenly spread.  Whole steps, sorted, staged /
+        // SORTED: the host knows what an even spread over the resident adapters puts into a block.  Whole steps, staged /
         // copied (block's ranks, gated ones doubled): Llama-8B 1024 tokens of 384 adapters (0.44 K) 836 / 820 us, 512 of 150
         // (0.56 K) 554 / 561, 512 of 285 (1.05 K) 657 / 681; Qwen2.5-7B 1024 of 200 (0.43 K) 985 / 936, 640 of 200 (0.68 K) 763 /
         // 830.  Gated, several rounds: Llama-8B 1500 of 128 (0.33 K) 1042 / 1000, 4000 of 384 (0.38 K) 2270 / 2167, 2048 of 384 (0.45 K)
         // 1176 / 1292.  Gated, up to two rounds, where the rows of the last block count for more: Llama-8B 1024 of 128 (0.30 K)
         // 698 / 690, 777 of 65 (0.33 K) 739 / 758, 1024 of 200 (0.46 K) 740 / 759.
+        // RUNS: adapters per block are anything from one to all, and the segment map knows.  Where all would be too many the kernels
+        // decide (ExpandTiles::long_chunks).
         const bool sorted = seg->mode == LORA_BUCKET_SORTED;
         const double blocks = std::max(1.0, (double)T / 256.0);
         const double ranks_each = (glu ? 2.0 : 1.0) * (double)c->ranks_resident / std::max(1, c->n_resident);
         const bool two_rounds = tiles_of(256, 256) <= 2L * c->n_cus;      // gate's and up's columns together, gated too
-        const bool direct = direct_ok && (!sa.on || ranks_each * std::min(256.0, 1.0 + c->n_resident / blocks) <= (!glu ? 0.45 : two_rounds ? 0.32 : 0.4) * K);
+        const bool direct = direct_ok && (!sa.on || !sorted || ranks_each * std::min(256.0, 1.0 + c->n_resident / blocks) <= (!glu ? 0.45 : two_rounds ? 0.32 : 0.4) * K);
         // Up to 64 tokens the tile has 32 or 64 rows; with more such tiles than CUs, the variant of which two workgroups
         // share a CU.
         auto small_variant = [&](int one, int pair, long tiles) { return tiles <= c->n_cus ? one : pair; };
@@ -1287,12 +1289,15 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         if ((over_byte_offsets((uint64_t)T, K) || over_byte_offsets((uint64_t)plan.n_max, K)) && !fused_wide_k(fv, glu)) fv = glu ? 8 : 10;
         const bool auto_direct = fused_direct(fv) && c->tune[LORA_TUNE_FUSED_VARIANT] == 0;
         if (fused_direct(fv) && !direct_ok) fv = 0;
+        int long_chunks = 0;
         if (auto_direct && fused_direct(fv) && sa.on) {
             // the staged tiles of the same shape
             const int staged = fv == kDirect192 ? kStaged192 : fv == kDirect128 ? kStaged128 : 0;
             const int rows = fv == kDirect128 ? 128 : 256, cols = fv == kDirect192 ? 192 : 256;
-            const double at_most = ranks_each * std::min<double>(rows, c->n_resident);
-            if (sorted && tiles_of(rows, cols) <= c->n_cus && at_most > 0.5 * K) {
+            const double at_most = ranks_each * std::min<double>(sorted ? rows : 256, c->n_resident);
+            if (!sorted) {
+                if (at_most > 0.6 * K) long_chunks = std::max(1, (int)(0.5 * K / 8.0 / (glu ? 2.0 : 1.0) * (double)((T + 255) / 256)));
+            } else if (tiles_of(rows, cols) <= c->n_cus && at_most > 0.5 * K) {
                 // A single round ends with the tile that has the most, and the rows of a mixed step's one-token requests have
                 // nearly all there are: 1300 tokens, 650 of them of 128 adapters of 8 to 64 ranks, Llama-8B q|k|v 154 us, staged 119.
                 fv = staged;
@@ -1338,6 +1343,7 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
         if (fused_direct(fv) && sa.on) {
             a.ex.on = 1;
             a.ex.returns = sorted ? 0 : 1;
+            a.ex.long_chunks = long_chunks;
             place_expand_tiles(a.ex, reinterpret_cast<char*>(part), n, T, c->cfg.max_rank);
             LaunchScope ls(c, s, "expand_tiles");
             if (HIP_FAIL(launch_expand_tiles(a, s))) return LORA_ERR_HIP;
@@ -1366,6 +1372,14 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
                                       : (fv == 0 || (fv >= 15 && fv <= 18) || fv == kStaged192 || fv == kStaged128)
                                           ? launch_gemm_staged_fused(a, fv == 0 ? 0 : fv >= kStaged192 ? fv - kStaged192 + 4 : fv - 15, s, &name)
                                                                           : launch_gemm_fused(a, fv == 12 ? 0 : fv, s, &name);
+            if (HIP_FAIL(le)) return LORA_ERR_HIP;
+            ls.rename(name);
+        }
+        if (a.ex.on && a.ex.long_chunks > 0) {
+            LaunchScope ls(c, s, "gemm_fused");
+            const char* name = nullptr;
+            const hipError_t le = glu ? launch_gemm_staged_glu(a, s, &name)
+                                      : launch_gemm_staged_fused(a, fv == kDirect192 ? 4 : fv == kDirect128 ? 5 : 0, s, &name);
             if (HIP_FAIL(le)) return LORA_ERR_HIP;
             ls.rename(name);
         }

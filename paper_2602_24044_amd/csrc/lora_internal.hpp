@@ -127,6 +127,9 @@ struct ShrinkArgs {
 struct ExpandTiles {
     int32_t on;          // 0: no adapter resident, nothing to expand
     int32_t returns;     // an adapter may come back within a block (RUNS)
+    int32_t long_chunks; // > 0: with more chunks than this, all blocks together, the register-staged kernel does the work; the
+                         // launches of both kernels are made, and one of them ends at once
+    int32_t pad_;
     int32_t* count;      // [blocks of 256 rows] chunks of eight ranks in the block
     int32_t* half;       // [2 blocks] of 128 rows of a block: the first chunk they use, rounded down to eight | the end << 16
     int32_t* row;        // [T] first chunk of the row's adapter in its block | chunks << 16

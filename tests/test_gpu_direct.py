@@ -266,6 +266,55 @@ def test_output_of_four_gigabytes(n_tokens, kernel):
     assert _launches(w) == [kernel]
 
 
+@pytest.mark.parametrize("n_tokens,cols,gated,kernel", [
+    (1300, 4096, False, "gemm_fused_direct_128x256x64_w4"),
+    (2100, 4104, False, "gemm_fused_direct_256x192x64_w4"),
+    (1025, 2056, True, "gemm_glu_direct_256x256x64_w4"),
+])
+def test_runs_of_few_and_many_adapters_on_one_captured_launch(n_tokens, cols, gated, kernel):
+    # 60 resident adapters of rank 8: in token order a block of rows may hold one of them or all.  The launches of both kernels
+    # are made and the block maps say which does the work: with more than 12 chunks per block (gated 6) the staged one
+    rng = np.random.default_rng(12)
+    few = np.repeat(np.arange(n_tokens // 100 + 1) % 60, 100)[:n_tokens]
+    many = rng.integers(-1, 60, size=n_tokens)
+    edge = np.concatenate([many[:256], np.full(n_tokens - 256, 3)])      # one block of many among blocks of one
+    proj = [(192, cols)] * (2 if gated else 1)
+    w = wl.custom("direct_or_staged", 5, proj, ["gate", "up"][:len(proj)], 60, 8, wl.BUCKET_RUNS, few.astype(np.int32), {i: 8 for i in range(60)})
+    sess = Session(w)
+    try:
+        sess.load(w.resident)
+
+        def step():
+            sess.bucket()
+            return sess.forward_glu(0, 1, out=sess.out[0]) if gated else sess.forward(0)
+
+        step()
+        assert B.lora_last_launches(sess.ctx) == ["shrink", "expand_tiles", kernel, STAGED[kernel]]
+        torch.cuda.synchronize()
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            step()
+        side.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            step()
+        for rep, ids in enumerate((many, few, many, edge, few)):
+            ids = ids.astype(np.int32)
+            sess.ids.copy_(torch.from_numpy(ids).to(sess.device))
+            sess.out[0].fill_(float("nan"))
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            if gated:
+                y_ref = oracle.gated(w.x[0], w.W[0], w.W[1], ids, oracle.adapters_of(w, 0), oracle.adapters_of(w, 1))
+            else:
+                y_ref = oracle.project(w.x[0], w.W[0], ids, oracle.adapters_of(w, 0))
+            assert rel_err(bf16_tensor_to_bits(sess.out[0]), y_ref) <= TOL, rep
+    finally:
+        sess.close()
+
+
 @pytest.mark.parametrize("n_tokens", [1100, 300])
 @pytest.mark.parametrize("variant", TILES)
 def test_captured_launch_on_new_token_ids(variant, n_tokens):
