@@ -351,8 +351,10 @@ enum {
     LORA_FUSED_STAGED_256x192x64_W8 = 30, /* smaller staged tiles, for grids that would leave the last round of the */
     LORA_FUSED_STAGED_128x256x64_W8 = 31, /* 256 x 256 ones mostly empty */
     /* 64-wide K tiles through the copy instruction, the expand as further K tiles, several output tiles per workgroup: what
-       LORA_FUSED_AUTO runs in place of the three staged shapes above unless K is below
-       192, the output reaches 4 GiB, the scratch is too small or the batch has very many adapters */
+       LORA_FUSED_AUTO runs in place of the three staged shapes above unless K is below 192, the output reaches 4 GiB, the
+       scratch is too small or the batch has very many adapters.  In token order (LORA_BUCKET_RUNS) only the device knows how
+       many meet in a block of rows: where all that are resident would be too many, the launches of both are made (and
+       logged), and one of them ends at once */
     LORA_FUSED_DIRECT_256x256x64_W4 = 33,
     LORA_FUSED_DIRECT_256x192x64_W4 = 34,
     LORA_FUSED_DIRECT_128x256x64_W4 = 35

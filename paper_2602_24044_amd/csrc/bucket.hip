@@ -297,8 +297,10 @@ __global__ __launch_bounds__(kBT) void bucket_kernel(BucketArgs a)
 // Steps of up to 64 W tokens: one token per lane of W waves.  Such a map is all latency: what the large kernel spends is its
 // fifteen barriers of sixteen waves and the scans over all keys.  Here a token's place is the number of tokens with a
 // smaller (key, index), counted against every other token, so that neither the number of keys nor a histogram matters; the
-// heads of segments and pieces are numbered from ballots; and the slot tables are read for the tokens' own slots only, in
-// the shadow of the counting.  Under the profiler, large kernel -> this one: 16 tokens
+// heads of segments and pieces are numbered from ballots; and the slot tables are read for the tokens' own slots only, as
+// the third of three loads in a row (id, slot, tables), behind which four waves count and one wave has little to count.  On
+// tables that no step has read yet, large kernel -> this one, by events around the launch: 32 tokens 10.2 -> 6.2 us, 99 tokens
+// 11.2 -> 6.2.  Under the profiler, in step after step: 16 tokens
 // 6.3 -> 3.1 us, 1 and 32 tokens of Llama-8B 7.1 -> 4.6, 99 tokens 7.3 -> 4.7, 256 tokens 10.2 -> 6.7.  Above 256 tokens the
 // counting (T compares per token) costs what it saves (512 tokens with eight waves 9.4 -> 9.1); RUNS counts nothing, and
 // sixteen waves serve it up to 1024 tokens (777 tokens 7.2 -> 5.0).

@@ -450,6 +450,9 @@ __device__ inline void expand_windows(f32x16 (&acc)[MB][NB], const int (&slot)[M
     }
 }
 
+// The gated MLP's activation, z sigmoid(z).
+__device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + __expf(-z)); }
+
 // More chunks of ranks in the launch's blocks than the host set as the limit (ExpandTiles::long_chunks).  The same for every wave.
 __device__ inline bool expand_is_long(const GemmArgs& a)
 {

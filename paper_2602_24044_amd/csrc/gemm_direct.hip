@@ -8,9 +8,14 @@
 //   - tiles copied global -> LDS by the copy instruction: no registers and no LDS writes in between (781 -> 725 us);
 //   - the copies spread evenly over the MFMAs, so that none waits for the CU's copy rate of 43 bytes a clock (-> 697);
 //   - 16x16x32 MFMAs: an accumulator is read and written once per 32 of K, not per 16 (K = 14336: 1388 -> 1465 TFLOP/s);
-//   - a workgroup keeps its CU and goes through several output tiles; its walk over K continues from one into the next, so
-//     that only the first waits for memory, and the expand is part of that walk (below), not a chain of memory latencies
-//     behind it.  The rows are stored past L2 (-> 650 us; 3 % more with adapters, where the other kernel's epilogue takes 10 %).
+//   - a workgroup keeps its CU and goes through several output tiles; the copies of its walk over K continue from one into the
+//     next, and the expand is part of that walk (below), not a chain of memory latencies behind it.  The rows are stored past
+//     L2 (-> 650 us; 3 % more with adapters, where the other kernel's epilogue takes 10 %).
+// What is left at a change of output tile: the wave waits for the data of the tile after the next on the spot, first for its
+// count of chunks, then for its rows, and the copies in flight land with them.  The 256 x 256 instances, whose accumulators take
+// half of the 512 registers, spill 10 to 13 of the others there and read them back behind the output stores, which so are
+// waited for in front of the next tile's first MFMAs; 256 x 192 spills at most one, 128 x 256 none.  All of them keep 8 to 27
+// spilled scalars in a vector register that the last K tiles fetch, which waits for the copies in flight too.
 // A round of 256 tiles over K = 4096: 256 x 256 112 -> 100 us (95 in a launch of several rounds), 256 x 192 90 -> 79,
 // 128 x 256 67.5 -> 59.
 //
@@ -85,8 +90,6 @@ __device__ __forceinline__ ArgsInPlace args_in_place()
     asm volatile("" : "+s"(p));
     return p;
 }
-
-__device__ __forceinline__ float direct_silu(float z) { return z / (1.0f + __expf(-z)); }
 
 // ---------------------------------------------------------------------------------------------------
 // The expand as a continuation of the walk over K.  Per block of kDBlock grouped rows the adapters' ranks stand side by side,
@@ -315,7 +318,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
         const int r = w_row(o, lane) - o * 8;
         woff[o] = (uint32_t)w_column(r) * (uint32_t)K * 2u + (uint32_t)(chunk_of(r + o * 8, lane) * 16);
     }
-    // What the copies and the epilogue of one output tile need; loaded two tiles ahead.  Per lane: of row l of the rows the
+    // What the copies and the epilogue of one output tile need; asked for two tiles ahead, and waited for there.  Per lane: of row l of the rows the
     // wave copies (8 XQ of them) the token and the chunks (ExpandTiles::row), the tokens of rows l and 64 + l of the wave's part of
     // the tile, record l % 8 of the tile's chunks.
     struct Info {
@@ -479,7 +482,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
                 __builtin_amdgcn_sched_barrier(0);
             });
             // this wave's last fragments of tile j are in registers; tile j + 1 has landed (W of tile j + 2 stays in flight,
-            // and so do the stores of the output tile before)
+            // and so do the stores of the output tile before, where no spilled register was read back behind them)
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             if (FIRST && stored) wait_copies_then_barrier<WQ + kStores>();
             else wait_copies_then_barrier<WQ>();
@@ -665,7 +668,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
                 if (GLU) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        y[c][e] = direct_silu(acc[w][(c >> 1) * 4 + (c & 1)][e]) * acc[w][((c >> 1) * 4 + 2 + (c & 1)) % NB][e];
+                        y[c][e] = silu_f32(acc[w][(c >> 1) * 4 + (c & 1)][e]) * acc[w][((c >> 1) * 4 + 2 + (c & 1)) % NB][e];
                 } else {
                     y[c] = acc[w][c];
                 }

@@ -248,8 +248,6 @@ __device__ __forceinline__ void finish_tile_prefetched(f32x16 (&acc)[MB][NB], co
 // results, then the activation and the product in fp32, one bf16 rounding, rows out through LDS.
 constexpr int glu_epilogue_bytes_per_wave() { return 2 * kPieceRows * kVStageStride * 2; }
 
-__device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + __expf(-z)); }
-
 template <int MB, int NB>
 __device__ __forceinline__ void finish_tile_glu(f32x16 (&acc)[MB][NB], const GemmArgs& a, const Slice& gate, const Slice& up,
                                                 int m_first, int n_first, int wave, uint16_t* ring)

@@ -8,10 +8,10 @@
 // instruction.  Measured on this chip, a CU fills its LDS through that instruction at 25 (four copying waves) to
 // 43 (eight) bytes per clock from L2-resident data, and ordinary loads reach 56 - 60; a 256 x 256 tile at the full
 // MFMA rate needs 64 KB per 2048 clocks = 32 bytes per clock, so the copy instruction, not the matrix cores, set
-// the pace of the eight-wave kernel that used it.  (With four waves that own 128 x 128 outputs each, half the LDS reads per
-// MFMA and several output tiles per workgroup, the copy instruction is the faster way, and the kernel built so serves what it
-// can of the large batches; this one serves the rest: short K, operands of 4 GiB, batches spread thinly over very many
-// adapters.)  Registers also hold the tile in flight, so two LDS stages are enough:
+// the pace of the eight-wave kernel that used it.  (With four waves that own 128 x 128 outputs each, two thirds of the
+// LDS reads per MFMA and several output tiles per workgroup, the copy instruction is the faster way, and the kernel built so
+// serves what it can of the large batches; this one serves the rest: short K, operands of 4 GiB, batches spread thinly over
+// very many adapters, of which in token order only the block maps know (expand_is_long).)  Registers also hold the tile in flight, so two LDS stages are enough:
 // tile j is multiplied out of one stage while tile j + 1 (on its way since the first K step of tile j - 1) is written
 // into the other during the first K step, and every register that write empties is refilled at once with its part of
 // tile j + 2, which so has a whole tile time to arrive (refilling in the second K step left three quarters of one).
