@@ -11,11 +11,10 @@
 //   - a workgroup keeps its CU and goes through several output tiles; the copies of its walk over K continue from one into the
 //     next, and the expand is part of that walk (below), not a chain of memory latencies behind it.  The rows are stored past
 //     L2 (-> 650 us; 3 % more with adapters, where the other kernel's epilogue takes 10 %).
-// What is left at a change of output tile: the wave waits for the data of the tile after the next on the spot, first for its
-// count of chunks, then for its rows, and the copies in flight land with them.  The 256 x 256 instances, whose accumulators take
-// half of the 512 registers, spill 10 to 13 of the others there and read them back behind the output stores, which so are
-// waited for in front of the next tile's first MFMAs; 256 x 192 spills at most one, 128 x 256 none.  All of them keep 8 to 27
-// spilled scalars in a vector register that the last K tiles fetch, which waits for the copies in flight too.
+// What is left at a change of output tile: the wave waits for the data of the tile after the next on the spot (128 x 256: first
+// for its range of chunks, then for its rows), and the copies in flight land with them.  The 256 x 256 instances, whose
+// accumulators take half of the 512 registers, spill 11 to 14 of the others there and read them back behind the output stores,
+// which so are waited for in front of the next tile's first MFMAs; 256 x 192 spills at most one, 128 x 256 none.
 // A round of 256 tiles over K = 4096: 256 x 256 112 -> 100 us (95 in a launch of several rounds), 256 x 192 90 -> 79,
 // 128 x 256 67.5 -> 59.
 //
@@ -354,6 +353,19 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
     };
     static_assert(BM == kDBlock || BM == kDBlock / 2, "a block or half of one");
     auto expand_tiles = [](int chunks) { return ((chunks >> 16) - (chunks & 0xffff) + 7) / 8 * (GLU ? 2 : 1); };
+    // Both.  A block's first chunk is its chunk 0, which saves the wait for the one in front of the other (q|k|v and o of
+    // Qwen2.5-7B at 4099 tokens 98 -> 96 us, 94 -> 92).
+    auto load_tile = [&](const Tile& t, const Tile& in_place, Info& f, int lane) {
+        const Tile of = t.on ? t : in_place;
+        if constexpr (BM == kDBlock) {
+            load_info(of, f, lane, 0);
+            return expand_chunks(t);
+        } else {
+            const int c = expand_chunks(t);
+            load_info(of, f, lane, c & 0xffff);
+            return c;
+        }
+    };
     auto x_buffer = [&](const Tile& t) {
         const ArgsInPlace ka = args_in_place();
         return buffer_of(ka->g.s[t.si].x, t.on ? (uint32_t)ka->dv.T * (uint32_t)K * 2u : 0u);
@@ -403,8 +415,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
             asm volatile("" : "+v"(xoff[q]));
         }
     };
-    int chunks = expand_chunks(cur);
-    load_info(cur, info, lane, chunks & 0xffff);
+    int chunks = load_tile(cur, cur, info, lane);
     u32x4 xrs = x_buffer(cur), wrs = w_buffer(cur, false), urs = GLU ? w_buffer(cur, true) : wrs;
     u32x4 xrs_next, wrs_next, urs_next;
     x_offsets(info, lane);
@@ -430,8 +441,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
     direct_for<WQ>([&](auto q) { copy_w(q, WST); });
     direct_for<XQ>([&](auto q) { copy_x(q, XST); });
     Tile nxt = next_tile();
-    int chunks_next = expand_chunks(nxt);
-    load_info(nxt.on ? nxt : cur, info_next, lane, chunks_next & 0xffff);
+    int chunks_next = load_tile(nxt, cur, info_next, lane);
     xrs_next = x_buffer(nxt);
     wrs_next = w_buffer(nxt, false);
     urs_next = GLU ? w_buffer(nxt, true) : wrs_next;
@@ -509,8 +519,7 @@ __global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs
         if (nxt.on) after = next_tile();
         int lr = lane;
         asm volatile("" : "+v"(lr));
-        const int chunks_after = expand_chunks(after);
-        load_info(after.on ? after : cur, info_after, lr, chunks_after & 0xffff);
+        const int chunks_after = load_tile(after, cur, info_after, lr);
         const u32x4 xrs_after = x_buffer(after), wrs_after = w_buffer(after, false), urs_after = GLU ? w_buffer(after, true) : wrs_after;
         int users = 0, users_next = 0;                       // per lane: windows that have chunk l % 8 of K tile j and of the next one
         auto last_tile = [&](int j, auto expand_c) __attribute__((always_inline)) {
