@@ -454,7 +454,7 @@ __device__ inline void expand_windows(f32x16 (&acc)[MB][NB], const int (&slot)[M
 __device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + __expf(-z)); }
 
 // More chunks of ranks in the launch's blocks than the host set as the limit (ExpandTiles::long_chunks).  The same for every wave.
-__device__ inline bool expand_is_long(const GemmArgs& a)
+__device__ inline bool expand_is_long(const LargeGemmArgs& a)
 {
     const int blocks = (a.dv.T + 255) / 256;
     int n = 0;

@@ -82,7 +82,7 @@ __device__ __forceinline__ void wait_copies_then_barrier()
 
 // The launch's arguments where they lie, for reads that are repeated for every tile: what is read through a pointer the
 // compiler cannot follow does not occupy scalar registers in between (it would spill them).
-typedef const __attribute__((address_space(4))) GemmArgs* ArgsInPlace;
+typedef const __attribute__((address_space(4))) LargeGemmArgs* ArgsInPlace;
 __device__ __forceinline__ ArgsInPlace args_in_place()
 {
     ArgsInPlace p = (ArgsInPlace)__builtin_amdgcn_kernarg_segment_ptr();
@@ -109,7 +109,7 @@ constexpr int kDBlock = 256;
 // shrink results in 7 chunks) 33.7 -> 7.3; 20462 tokens 5.4 - 8.9 -> 5.3.
 constexpr int kDShares = kDBlock / 32;
 constexpr int kDChunks = 4;                                   // shrink chunks per round of loads
-__global__ __launch_bounds__(kDBlock) void expand_tiles_kernel(GemmArgs a)
+__global__ __launch_bounds__(kDBlock) void expand_tiles_kernel(LargeGemmArgs a)
 {
     __shared__ int s_wave[2][kDBlock / kWave], s_range[kDBlock / kWave];
     __shared__ __attribute__((aligned(16))) int s_loc[kDBlock];   // per run: its adapter's location; behind the last: -1
@@ -234,7 +234,7 @@ constexpr uint32_t kNowhere = 0xffffff00u;                   // an offset behind
 
 // BIAS: some slice of the launch has a bias (an instance of its own, so that the others carry nothing for it).
 template <int BM, int BN, bool GLU, bool BIAS>
-__global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(GemmArgs a)
+__global__ __launch_bounds__(kDWaves* kWave, 1) void gemm_direct_kernel(LargeGemmArgs a)
 {
     constexpr int WTM = BM / 2, WTN = BN / 2;               // wave tile: 2 x 2 waves
     constexpr int MB = WTM / kDB, NB = WTN / kDB;           // accumulator blocks per wave
@@ -751,7 +751,7 @@ int tile_turn(int tiles_m, int grid)
 }
 
 template <int BM, int BN, bool GLU, bool BIAS>
-hipError_t launch_direct(GemmArgs a, int n_cus, hipStream_t stream)
+hipError_t launch_direct(LargeGemmArgs a, int n_cus, hipStream_t stream)
 {
     a.tiles_m = (a.m_end - a.m_begin + BM - 1) / BM;
     a.tiles_n = 0;
@@ -772,18 +772,18 @@ hipError_t launch_direct(GemmArgs a, int n_cus, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_expand_tiles(const GemmArgs& a, hipStream_t stream)
+hipError_t launch_expand_tiles(const LargeGemmArgs& a, hipStream_t stream)
 {
     hipLaunchKernelGGL(expand_tiles_kernel, dim3((a.dv.T + kDBlock - 1) / kDBlock, a.g.n, kDShares + 1), dim3(kDBlock), 0, stream, a);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_direct_glu(const GemmArgs& a, int n_cus, hipStream_t stream)
+hipError_t launch_gemm_direct_glu(const LargeGemmArgs& a, int n_cus, hipStream_t stream)
 {
     return launch_direct<256, 256, true, false>(a, n_cus, stream);
 }
 
-hipError_t launch_gemm_direct_fused(const GemmArgs& a, int tile, int n_cus, hipStream_t stream)
+hipError_t launch_gemm_direct_fused(const LargeGemmArgs& a, int tile, int n_cus, hipStream_t stream)
 {
     bool bias = false;
     for (int k = 0; k < a.g.n; ++k) bias = bias || a.g.s[k].bias != nullptr;

@@ -56,7 +56,7 @@ __device__ inline void lds_done_then_barrier()
 // between the two matrices in blocks of 32 rows and a workgroup owns BN / 2 output columns (as in the 64-wide-K
 // kernel for small batches).
 template <int BM, int BN, int WGM, int WGN, int PG, bool GLU = false>
-__global__ __launch_bounds__(WGM* WGN* kWave) void gemm_staged_kernel(GemmArgs a)
+__global__ __launch_bounds__(WGM* WGN* kWave) void gemm_staged_kernel(LargeGemmArgs a)
 {
     constexpr int NWV = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;           // wave tile
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_staged_kernel(GemmArgs a
 }
 
 template <int BM, int BN, int WGM, int WGN, int PG, bool GLU = false>
-hipError_t launch_staged(GemmArgs a, hipStream_t stream)
+hipError_t launch_staged(LargeGemmArgs a, hipStream_t stream)
 {
     a.tiles_m = (a.m_end - a.m_begin + BM - 1) / BM;
     a.tiles_n = 0;
@@ -280,13 +280,13 @@ hipError_t launch_staged(GemmArgs a, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_gemm_staged_glu(const GemmArgs& a, hipStream_t stream, const char** name)
+hipError_t launch_gemm_staged_glu(const LargeGemmArgs& a, hipStream_t stream, const char** name)
 {
     *name = "gemm_glu_staged_256x256x64_w8";
     return launch_staged<256, 256, 2, 4, 1, true>(a, stream);
 }
 
-hipError_t launch_gemm_staged_fused(const GemmArgs& a, int variant, hipStream_t stream, const char** name)
+hipError_t launch_gemm_staged_fused(const LargeGemmArgs& a, int variant, hipStream_t stream, const char** name)
 {
     switch (variant) {
         case 1:

@@ -1336,10 +1336,11 @@ lora_status forward_impl(lora_ctx* c, int32_t layer, int32_t n, const int32_t* p
             LaunchScope ls(c, s, "shrink");
             if (HIP_FAIL(launch_shrink(sa, grid, s))) return LORA_ERR_HIP;
         }
-        GemmArgs a = ga;
+        LargeGemmArgs a;
+        std::memset(&a, 0, sizeof a);
+        static_cast<GemmArgs&>(a) = ga;
         a.m_end = m_split;
         a.shrink_front = front;
-        a.ex.on = 0;
         if (fused_direct(fv) && sa.on) {
             a.ex.on = 1;
             a.ex.returns = sorted ? 0 : 1;

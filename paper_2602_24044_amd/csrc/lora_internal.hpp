@@ -122,27 +122,9 @@ struct ShrinkArgs {
     int32_t on;          // 0: nothing to shrink (no adapter resident)
 };
 
-// What the GEMM kernel for large batches needs to run the expand as further K tiles (gemm_direct.hip), written by a small
-// launch in front of it into scratch of the call.
-struct ExpandTiles {
-    int32_t on;          // 0: no adapter resident, nothing to expand
-    int32_t returns;     // an adapter may come back within a block (RUNS)
-    int32_t long_chunks; // > 0: with more chunks than this, all blocks together, the register-staged kernel does the work; the
-                         // launches of both kernels are made, and one of them ends at once
-    int32_t pad_;
-    int32_t* count;      // [blocks of 256 rows] chunks of eight ranks in the block
-    int32_t* half;       // [2 blocks] of 128 rows of a block: the first chunk they use, rounded down to eight | the end << 16
-    int32_t* row;        // [T] first chunk of the row's adapter in its block | chunks << 16
-    int2* record;        // [blocks][256 max_rank / 8] location of the adapter, its rank | first of the chunk's ranks << 8 |
-                         // the block's windows of 16 rows that have it << 16
-    int32_t* zero;       // [4] zeros
-    uint16_t* v;         // [slices][T][max_rank] bf16: scaled shrink results
-};
-
 struct GemmArgs {
     DeviceView dv;
     GroupArgs g;
-    ExpandTiles ex;
     int32_t K;
     int32_t tiles_m, tiles_n;   // tiles_n counts the tiles of all slices
     int32_t split_k;     // 1 on the fused path
@@ -163,11 +145,38 @@ struct GemmArgs {
     int32_t shrink_front;
     int32_t front_expect;       // reports the tile workgroups wait for: shrink_front (one more in the host-forced test of the expired wait)
     int32_t wait_spins;         // polls of the bounded wait
-    int32_t turn;               // gemm_direct.hip: places by which the deal of the tiles turns from round to round
     int32_t k_rot;              // 64-wide-K kernels, fused path: column tiles start their walk over K at different places
     uint32_t* sync;
     uint32_t* flags;
 };
+
+// What the GEMM kernel for large batches needs to run the expand as further K tiles (gemm_direct.hip), written by a small
+// launch in front of it into scratch of the call.
+struct ExpandTiles {
+    int32_t on;          // 0: no adapter resident, nothing to expand
+    int32_t returns;     // an adapter may come back within a block (RUNS)
+    int32_t long_chunks; // > 0: with more chunks than this, all blocks together, the register-staged kernel does the work; the
+                         // launches of both kernels are made, and one of them ends at once
+    int32_t pad_;
+    int32_t* count;      // [blocks of 256 rows] chunks of eight ranks in the block
+    int32_t* half;       // [2 blocks] of 128 rows of a block: the first chunk they use, rounded down to eight | the end << 16
+    int32_t* row;        // [T] first chunk of the row's adapter in its block | chunks << 16
+    int2* record;        // [blocks][256 max_rank / 8] location of the adapter, its rank | first of the chunk's ranks << 8 |
+                         // the block's windows of 16 rows that have it << 16
+    int32_t* zero;       // [4] zeros
+    uint16_t* v;         // [slices][T][max_rank] bf16: scaled shrink results
+};
+
+// Of the kernels for large batches (gemm_direct.hip, gemm_staged.hip).  Apart from GemmArgs, which the kernels of small batches
+// take together with ShrinkArgs: with these fields in it their arguments were 1224 bytes instead of 1160, and the first forward
+// call on a context took the HIP runtime longer for it.  First step of a new context, 1224 -> 1160 bytes (the same kernels, host time
+// of the first call in brackets): Llama-8B 32 tokens 228 -> 210 us (38 -> 21), 99 tokens on four layers 820 - 880 -> 780 - 800 (60 - 120 -> 20 - 45).
+struct LargeGemmArgs : GemmArgs {
+    ExpandTiles ex;
+    int32_t turn;               // gemm_direct.hip: places by which the deal of the tiles turns from round to round
+    int32_t pad_;
+};
+static_assert(sizeof(GemmArgs) + sizeof(ShrinkArgs) <= 1160, "arguments of the small batches' kernels: see LargeGemmArgs");
 
 struct ReduceArgs {
     DeviceView dv;
@@ -195,13 +204,13 @@ hipError_t launch_gemm_rows128_splitk(const GemmArgs& a, const ShrinkArgs& sa, i
 // large batches: tiles staged through registers (ordinary loads + LDS writes)
 hipError_t launch_gemm_rows128_glu(const GemmArgs& a, const ShrinkArgs& none, int variant, hipStream_t stream,
                                    const char** name);
-hipError_t launch_gemm_staged_glu(const GemmArgs& a, hipStream_t stream, const char** name);
-hipError_t launch_gemm_staged_fused(const GemmArgs& a, int variant, hipStream_t stream, const char** name);
+hipError_t launch_gemm_staged_glu(const LargeGemmArgs& a, hipStream_t stream, const char** name);
+hipError_t launch_gemm_staged_fused(const LargeGemmArgs& a, int variant, hipStream_t stream, const char** name);
 // large batches: tiles copied straight to LDS, the expand as further K tiles (what those need is written by
 // launch_expand_tiles, in front, when a.ex.on); tile 0: 256 x 256, 1: 256 x 192, 2: 128 x 256
-hipError_t launch_expand_tiles(const GemmArgs& a, hipStream_t stream);
-hipError_t launch_gemm_direct_fused(const GemmArgs& a, int tile, int n_cus, hipStream_t stream);
-hipError_t launch_gemm_direct_glu(const GemmArgs& a, int n_cus, hipStream_t stream);
+hipError_t launch_expand_tiles(const LargeGemmArgs& a, hipStream_t stream);
+hipError_t launch_gemm_direct_fused(const LargeGemmArgs& a, int tile, int n_cus, hipStream_t stream);
+hipError_t launch_gemm_direct_glu(const LargeGemmArgs& a, int n_cus, hipStream_t stream);
 hipError_t launch_reduce_expand(const ReduceArgs& a, int grid, hipStream_t stream);
 
 }  // namespace lora
